@@ -1,7 +1,9 @@
 """Build the gfx950 HIP library (libmdgpu.so) in-tree with hipcc.
 
 All HIP code is compiled for gfx950 only, with packed-FP32 instruction
-selection switched off (-target-feature -packed-fp32-ops).
+selection switched off (-target-feature -packed-fp32-ops), and with matrix
+products accumulating in vector registers (-amdgpu-mfma-vgpr-form: results in
+accumulation registers cost a move each before the vector ALU can read them).
 """
 import os
 import subprocess
@@ -15,7 +17,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         "-munsafe-fp-atomics", "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
+         "-munsafe-fp-atomics", "-mllvm", "-amdgpu-mfma-vgpr-form", "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
          "-Wno-unknown-pragmas"]
 
 

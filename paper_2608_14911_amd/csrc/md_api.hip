@@ -196,6 +196,14 @@ static double fixed_band(double r2, double Lmax) {
     return 4.0 * (2.0 * sqrt(3.0) * r * 2.0 * eq + (4.0 * sqrt(3.0) + 4.0) * 0x1.0p-24 * r2);
 }
 
+// Whether the matrix-core list build can serve the configuration.
+static bool mat_build_fits(const md_config* c, const Geom* g) {
+    if (c->flags & MD_CFG_NL_PER_PARTICLE) return false;
+    for (int d = 0; d < 3; ++d)
+        if (g->nc[d] < 2 * g->kc + 2) return false;
+    return true;
+}
+
 static md_status plan_geom(const md_config* c, Geom* g, std::string* why) {
     md_status st = validate(c, why);
     if (st != MD_OK) return st;
@@ -271,29 +279,18 @@ static md_status plan_geom(const md_config* c, Geom* g, std::string* why) {
     g->skin = c->skin;
     g->table_points = c->table_points;
     if (g->le) g->nl_tile = 0;   // the sheared stencil is built one particle per lane
-    g->nl_cubic = (c->box[0] == c->box[1] && c->box[1] == c->box[2]) ? 1 : 0;
+    // Matrix-core build from 5 particles per cell of side rv on: it tests a
+    // tile's whole row of candidates, the per-particle build only a lane's own
+    // 27 cells.  Measured per build: 6.6 per cell (sheared DPD fluid, 1M) 217
+    // against 386 us, 19 per cell (LJ fluid, 1M) 326 us; 3.1 per cell (melt,
+    // 2M) 472 against 396 us.  Its coordinates relative to a segment's centre
+    // are minimum images only with 2 kc + 2 cells per side; smaller boxes build
+    // one particle per lane.
+    g->nl_mat = (density * rv * rv * rv >= 5.0 || (c->flags & MD_CFG_NL_TILES)) && mat_build_fits(c, g) ? 1 : 0;
     // the unbonded fast step kernel gathers 12-byte records (fewer L1 lines per
     // gather: 4% faster on the LJ fluid); the bonded one keeps the 16-byte
     // records, for which the extra stores cost more than the gathers save
     g->x3_on = (c->n_bonds == 0 && c->n_angles == 0) ? 1 : 0;
-    {
-        // rv^2 -/+ band over ql^2 (ql = L 2^-32 exactly), rounded outwards to float
-        const double ql = c->box[0] * 0x1.0p-32;
-        const double lo = (g->rv2 - band) / (ql * ql), hi = (g->rv2 + band) / (ql * ql);
-        float flo = (float)lo, fhi = (float)hi;
-        if ((double)flo > lo) flo = nextafterf(flo, 0.0f);
-        if ((double)fhi < hi) fhi = nextafterf(fhi, INFINITY);
-        g->rq2lo = flo;
-        g->rq2hi = fhi;
-        // 16-bit prefilter: dx16 = (int32)(q_j - q_i) >> 16 is within e = U + ql
-        // of the FP64 difference (U = L 2^-16), so |r16^2 U^2 - r^2| stays
-        // below 2 rv sqrt(3) e + 3 e^2 around rv; 1.5x that, rounded outwards
-        const double U = c->box[0] * 0x1.0p-16, e = U + ql;
-        const double B16 = 1.5 * (2.0 * rv * sqrt(3.0) * e + 3.0 * e * e);
-        const double l16 = floor((g->rv2 - B16) / (U * U)), h16 = ceil((g->rv2 + B16) / (U * U));
-        g->r16lo = (uint32_t)fmax(0.0, fmin(l16, 4294967295.0));
-        g->r16hi = (uint32_t)fmax(0.0, fmin(h16, 4294967295.0));
-    }
     return MD_OK;
 }
 
@@ -1621,6 +1618,11 @@ md_status md_batch_init(const md_config* cfgs, int32_t nsys, const double* const
             md_batch_destroy(b);
             return fail(nullptr, r, m);
         }
+        // one build kernel for all members wherever it fits: sparse members
+        // alone would build faster per particle, but a second launch's tail
+        // costs more (48 uneven replicas: 93 us per step in one kernel, 69 + 68
+        // us in two)
+        h->g.nl_mat = mat_build_fits(&cfgs[s], &h->g) ? 1 : 0;
         b->sys.push_back(h);
     }
     std::vector<SysEntry> tab((size_t)4 * nsys);
@@ -1641,6 +1643,8 @@ md_status md_batch_init(const md_config* cfgs, int32_t nsys, const double* const
                 e.c_off = p.c_off[s];
             }
         for (int64_t t = 0; t < p.ntiles[s]; ++t) tiles[p.tile0[s] + t] = s;
+        if (h->g.nl_mat) b->bc.any_mat = 1;
+        else b->bc.any_one = 1;
     }
     if (hipMemcpyAsync(b->tabs[0][0], tab.data(), sizeof(SysEntry) * tab.size(), hipMemcpyHostToDevice,
                        b->stream) != hipSuccess ||

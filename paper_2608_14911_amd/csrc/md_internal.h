@@ -94,13 +94,9 @@ struct Geom {
     double qs[3];           // 2^32 / L
     float ql[3];            // L / 2^32
     float rv2lo, rv2hi;     // fixed-point list test band; FP64 test in between
-    int32_t nl_tile;        // list build: 1 = one wavefront per 64-particle tile with
-                            // candidates broadcast through the scalar cache, 0 = one
-                            // particle per lane
-    int32_t nl_cubic;       // cubic box: the tile build tests r^2 in fixed-point units
-    float rq2lo, rq2hi;     // the list band in units of (L 2^-32)^2 (cubic box)
-    uint32_t r16lo, r16hi;  // a wider band in units of (L 2^-16)^2 for the 16-bit
-                            // prefilter of the tile build (cubic box)
+    int32_t nl_tile;        // the plan's list build (md_plan.nl_build)
+    int32_t nl_mat;         // the list is built on the matrix cores, one wavefront per
+                            // 64-particle tile; 0: one particle per lane
     int32_t x3_on;          // keep the 12-byte position records (systems without bonds,
                             // whose fast step kernel gathers them)
     // Lees-Edwards shear (flow x, gradient y): offset delta(step) =
@@ -317,6 +313,7 @@ struct BatchCells {
     int64_t* c_off;         // [nsys + 1] first cell per system
     int32_t* base;          // [nsys] scan prefix at each system's first cell
     int32_t nsys;
+    int32_t any_mat, any_one;   // some member's list is built on the matrix cores / per particle
 };
 
 // ev_sorted (or null) is recorded between the cell sort and the list build

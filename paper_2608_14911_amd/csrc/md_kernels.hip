@@ -750,229 +750,6 @@ __global__ void __launch_bounds__(kBlock) k_nl_build(Geom g, Bufs b, int parity,
     nl_epilogue(b, local_max, overflow);
 }
 
-// The same lists built one wavefront per 64-particle tile of the sorted order
-// (the tile of the list layout).  The tile's particles lie in a few
-// consecutive cells; lanes of one (y, z) cell row form a segment whose x-cells
-// span [x0, x1].  The segment's candidates are the particles of cells
-// [x0 - kc, x1 + kc] in each of the (2kc+1)^2 neighbouring rows, streamed in
-// nl_one's order (rows z-major, a wrapped x-range high part first, sorted
-// index) through the scalar cache: every lane tests every candidate, so there
-// are no per-lane gathers.  A candidate outside a lane's own stencil is at
-// least kc cell sides >= rv away and never passes the test, and a lane's own
-// candidates keep their relative order, so each row equals nl_one's entry for
-// entry.  A segment is cut where its x-span plus the stencil would exceed the
-// row (no candidate twice).  Cubic boxes prefilter on the upper 16 bits of
-// the fixed-point differences with integer r^2 (two 24-bit multiplies of
-// sign-extended upper words per axis), with a band that bounds the
-// truncation; inside it the 32-bit test and then FP64 decide.
-typedef int int4v __attribute__((ext_vector_type(4)));
-typedef const __attribute__((address_space(4))) int4v* __restrict__ scalar_int4_ptr;
-typedef const __attribute__((address_space(4))) int32_t* __restrict__ scalar_i32_ptr;
-
-// Row builder state of one lane (one particle of a tile): its fixed-point
-// and FP64 position, its row in the tile's list block and the row length.
-struct NlRow {
-    uint32_t qx, qy, qz;
-    double4 xi;
-    int self, cnt, cap;
-    char* tnlb;          // byte base of the tile's list block (32-bit offsets from it)
-    uint32_t lane4;
-
-    // A hit goes to slot min(cnt, cap - 1): an overflowing row overwrites its
-    // last slot, and the overflow flag then voids the list.
-    __device__ __forceinline__ void hit(int j) {
-        const int slot = cnt < cap ? cnt : cap - 1;
-        *(uint32_t*)(tnlb + (((uint32_t)slot << 8) | lane4)) = (uint32_t)j;
-        ++cnt;
-    }
-
-    // Candidate j at fixed-point position qj, counted when ok.  All lanes of
-    // the wavefront call it together (the band test is a wavefront mask).
-    template <bool CUBIC>
-    __device__ __forceinline__ void test(const Geom& g, const double4* __restrict__ x, int j, const int4v qj,
-                                         bool ok) {
-        const int lane = threadIdx.x & 63;
-        if (CUBIC) {
-            // 16-bit prefilter: the high halves of the fixed-point differences
-            // (24-bit multiplies of the upper words), decided outside a band
-            // that bounds its truncation; inside it the 32-bit test, then FP64
-            const int32_t ex = (int32_t)((uint32_t)qj.x - qx), ey = (int32_t)((uint32_t)qj.y - qy),
-                          ez = (int32_t)((uint32_t)qj.z - qz);
-            const int hx = ex >> 16, hy = ey >> 16, hz = ez >> 16;
-            const uint32_t r16 = (uint32_t)__mul24(hx, hx) + (uint32_t)__mul24(hy, hy) + (uint32_t)__mul24(hz, hz);
-            if (ok && r16 < g.r16lo && j != self) hit(j);
-            // lanes with r16 in [lo, hi): one unsigned compare, as a wave mask
-            const uint64_t band = __builtin_amdgcn_uicmp(r16 - g.r16lo, g.r16hi - g.r16lo, 36 /* ult */);
-            if (__builtin_expect(band != 0, 0)) {
-                if (ok && ((band >> lane) & 1)) {
-                    const float dx = (float)ex, dy = (float)ey, dz = (float)ez;
-                    const float r2 = dx * dx + dy * dy + dz * dz;
-                    bool in = r2 < g.rq2lo;
-                    if (!in && r2 < g.rq2hi) in = exact_r2(g, xi, x[j]) < g.rv2;
-                    if (in && j != self) hit(j);
-                }
-            }
-        } else {
-            const float dx = qdiff((uint32_t)qj.x, qx, g.ql[0]);
-            const float dy = qdiff((uint32_t)qj.y, qy, g.ql[1]);
-            const float dz = qdiff((uint32_t)qj.z, qz, g.ql[2]);
-            const float r2 = dx * dx + dy * dy + dz * dz;
-            if (ok && r2 < g.rv2lo && j != self) hit(j);
-            const uint64_t band = __builtin_amdgcn_uicmp(__float_as_uint(r2) - __float_as_uint(g.rv2lo),
-                                                         __float_as_uint(g.rv2hi) - __float_as_uint(g.rv2lo), 36);
-            if (__builtin_expect(band != 0, 0)) {
-                if (ok && ((band >> lane) & 1) && exact_r2(g, xi, x[j]) < g.rv2 && j != self) hit(j);
-            }
-        }
-    }
-};
-
-// Lane setup shared by the tile builds: particle p = t*64 + lane, its cell
-// and its row state.
-__device__ __forceinline__ NlRow nl_row_setup(const Geom& g, const Bufs& b, int64_t t, int parity, bool valid,
-                                              int& cxl, int& cyl, int& czl) {
-    const int lane = threadIdx.x & (kTile - 1);
-    const int64_t p = t * kTile + lane;
-    NlRow r;
-    r.qx = r.qy = r.qz = 0;
-    r.xi = make_double4(0.0, 0.0, 0.0, 0.0);
-    cxl = cyl = czl = -1;
-    if (valid) {
-        r.xi = b.x[parity][p];
-        cell_coords(g, r.xi.x, r.xi.y, r.xi.z, cxl, cyl, czl);
-        const int4 q = b.xq[parity][p];
-        r.qx = (uint32_t)q.x;
-        r.qy = (uint32_t)q.y;
-        r.qz = (uint32_t)q.z;
-    }
-    r.self = (int)p;
-    r.cnt = 0;
-    r.cap = g.cap;
-    r.tnlb = (char*)(b.nl + t * (int64_t)g.cap * kTile);
-    r.lane4 = (uint32_t)lane << 2;
-    return r;
-}
-
-// Row count, padding to a multiple of 8 with the particle itself, and the
-// bonded remap.
-__device__ __forceinline__ void nl_row_finish(const Geom& g, const Bufs& b, const NlRow& r, bool valid, int bonded,
-                                              int& local_max, bool& overflow) {
-    if (!valid) return;
-    const int64_t p = r.self;
-    b.ncount[p] = r.cnt;
-    if (r.cnt > local_max) local_max = r.cnt;
-    if (r.cnt > g.cap) overflow = true;
-    for (int k = r.cnt; k < ((r.cnt + 7) & ~7) && k < g.cap; ++k)
-        *(uint32_t*)(r.tnlb + (((uint32_t)k << 8) | r.lane4)) = (uint32_t)p;
-    if (bonded) remap_bonded(b, g.n, p);
-}
-
-template <bool CUBIC>
-__device__ __forceinline__ void nl_tile(const Geom& g, const Bufs& b, int64_t t, int parity, int bonded,
-                                        int& local_max, bool& overflow) {
-    const int lane = threadIdx.x & (kTile - 1);
-    const int64_t n = g.n;
-    const int nv = (n - t * kTile < kTile) ? (int)(n - t * kTile) : kTile;
-    const bool valid = lane < nv;
-    const double4* __restrict__ x = b.x[parity];
-    // the particle data are not written by this kernel: uniform loads through
-    // the constant address space become scalar loads
-    const scalar_int4_ptr xqs = (scalar_int4_ptr)(const void*)b.xq[parity];
-    const scalar_i32_ptr cs = (scalar_i32_ptr)(const void*)b.cstart;
-    const int kc = g.kc, nx = g.nc[0];
-    int cxl, cyl, czl;
-    NlRow row = nl_row_setup(g, b, t, parity, valid, cxl, cyl, czl);
-    // candidates [j, e) through the scalar cache, 8 and 4 at a time; the
-    // next batch of 8 is loaded before the current one is tested, so its
-    // scalar-cache latency overlaps the tests (measured: 697 -> 643 us per
-    // LJ-1M build)
-    auto scan = [&](int j, const int e) {
-        if (j + 8 <= e) {
-            int4v q[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) q[u] = xqs[j + u];
-            for (; j + 16 <= e; j += 8) {
-                int4v nq[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) nq[u] = xqs[j + 8 + u];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) row.test<CUBIC>(g, x, j + u, q[u], true);
-#pragma unroll
-                for (int u = 0; u < 8; ++u) q[u] = nq[u];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) row.test<CUBIC>(g, x, j + u, q[u], true);
-            j += 8;
-        }
-        for (; j + 4 <= e; j += 4) {
-            const int4v q0 = xqs[j], q1 = xqs[j + 1], q2 = xqs[j + 2], q3 = xqs[j + 3];
-            row.test<CUBIC>(g, x, j, q0, true);
-            row.test<CUBIC>(g, x, j + 1, q1, true);
-            row.test<CUBIC>(g, x, j + 2, q2, true);
-            row.test<CUBIC>(g, x, j + 3, q3, true);
-        }
-        for (; j < e; ++j) row.test<CUBIC>(g, x, j, xqs[j], true);
-    };
-    int lo = 0;
-    while (lo < nv) {
-        const int x0 = __builtin_amdgcn_readlane(cxl, lo);
-        const int y0 = __builtin_amdgcn_readlane(cyl, lo);
-        const int z0 = __builtin_amdgcn_readlane(czl, lo);
-        const int xlim = x0 + nx - 2 * kc - 1;
-        const int hi = lo + (int)__popcll(__ballot(valid && lane >= lo && cyl == y0 && czl == z0 && cxl <= xlim));
-        const int x1 = __builtin_amdgcn_readlane(cxl, hi - 1);
-        if (lane >= lo && lane < hi) {
-            const int xa = x0 - kc, xb = x1 + kc;
-            const bool wl = xa < 0, wh = xb >= nx;
-            const int side = 2 * kc + 1, np = 2 * side * side;
-            // piece p: the first or second range of stencil row p / 2 (rows
-            // z-major); the next piece's bounds are loaded before the
-            // current piece is scanned
-            auto piece = [&](int p, int& a, int& e) {
-                a = e = 0;
-                const int r = p >> 1, pc = p & 1;
-                const int nz = wrapc(z0 + r / side - kc, g.nc[2]), ny = wrapc(y0 + r % side - kc, g.nc[1]);
-                const int64_t rowc = ((int64_t)nz * g.nc[1] + ny) * nx;
-                if (!wl && !wh) {
-                    if (pc == 0) { a = cs[rowc + xa]; e = cs[rowc + xb + 1]; }
-                } else if (wl) {
-                    if (pc == 0) { a = cs[rowc + nx + xa]; e = cs[rowc + nx]; }
-                    else { a = cs[rowc]; e = cs[rowc + xb + 1]; }
-                } else {
-                    if (pc == 0) { a = cs[rowc + xa]; e = cs[rowc + nx]; }
-                    else { a = cs[rowc]; e = cs[rowc + xb - nx + 1]; }
-                }
-            };
-            int pa, pe;
-            piece(0, pa, pe);
-            for (int p = 0; p < np; ++p) {
-                int na = 0, ne = 0;
-                if (p + 1 < np) piece(p + 1, na, ne);
-                scan(pa, pe);
-                pa = na;
-                pe = ne;
-            }
-        }
-        lo = hi;
-    }
-    nl_row_finish(g, b, row, valid, bonded, local_max, overflow);
-}
-
-constexpr int kNlBlock = kBlock;
-__global__ void __launch_bounds__(kNlBlock) k_nl_tiles(Geom g, Bufs b, int parity, int bonded) {
-    if (!rebuild_requested(b)) return;
-    // wave-uniform tile index (readfirstlane keeps it in scalar registers)
-    const int64_t t = (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kNlBlock / kTile) +
-                      __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kTile));
-    int local_max = 0;
-    bool overflow = false;
-    if (t * kTile < g.n) {
-        if (g.nl_cubic) nl_tile<true>(g, b, t, parity, bonded, local_max, overflow);
-        else nl_tile<false>(g, b, t, parity, bonded, local_max, overflow);
-    }
-    nl_epilogue(b, local_max, overflow);
-}
-
 // ------------------------------------------------------------------ Lees-Edwards shear
 //
 // Flow along x, gradient along y (section "New Features": Lees-Edwards
@@ -1150,6 +927,364 @@ __global__ void __launch_bounds__(kBlock) k_nl_build_le(Geom g, Bufs b, int pari
     bool overflow = false;
     for (int64_t i = gtid_xcd(); i < g.n; i += gstride())
         nl_one_le(g, b, i, parity, bonded, delta, dw, qd, local_max, overflow);
+    nl_epilogue(b, local_max, overflow);
+}
+
+// ------------------------------------------------------------------ list build on the matrix cores
+//
+// The lists of nl_one (and nl_one_le) built one wavefront per 64-particle tile
+// of the sorted order (the tile of the list layout), entry for entry.  The
+// tile's particles lie in a few consecutive cells; lanes of one (y, z) cell row
+// form a segment whose x-cells span [x0, x1].  The segment's candidates are
+// the particles of cells [x0 - kc, x1 + kc] in each of the (2kc+1)^2
+// neighbouring rows, in nl_one's order (rows z-major, a wrapped x-range high
+// part first, sorted index), taken 32 at a time over the ends of the ranges.
+// A candidate outside a lane's own stencil is at least kc cell sides >= rv
+// away and never passes the test, and a lane's own candidates keep their
+// relative order.
+//
+// The squared distances of 32 candidates to the tile's 64 particles are a
+// contraction of length 4, (x, y, z, |r_j|^2) . (-2x, -2y, -2z, 1), on
+// coordinates relative to the segment's centre: four
+// v_mfma_f32_32x32x2_f32 with |r_i|^2 - rv^2 as the accumulator's start, so
+// that the sign bit of the result is the list test.  One v_alignbit per result
+// collects the sign bits, one v_min3 per two results the distance to the
+// threshold; a chunk that comes within the rounding bound of it (nl_delta) is
+// retaken in FP64 for the candidates concerned, so the sets are those of the
+// FP64 definition.  Coordinates relative to the centre are the minimum image
+// only where half the segment and rv together stay below half the box: a
+// segment spans at most nx - 2kc - 1 cells, and the build needs 2kc + 2 cells
+// per side (Geom::nl_mat).
+//
+// The hits of 32 candidates are one 32-bit word per lane.  Each lane queues
+// its words with hits in LDS (W of them), then all lanes write their rows
+// together, slot by slot, as whole 256-byte stores.  Writing each hit when it
+// is found cost the texture path 625 partly masked stores per tile and sent
+// the list through the L2 4.2 times (1.44 GB for 344 MB at 1M particles).
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+constexpr int kNlSpan = 31;     // x-cells of a segment beyond its first: bounds the coordinates, so the rounding
+// Words a lane queues before the rows are written: 18 let 16 wavefronts share
+// a CU's LDS, as many as the registers allow.  A particle of a dense fluid (19
+// per cell) has hits in 20-30 words; 23 words (12 wavefronts) took 363 us per
+// 1M-particle build, 14 words 344, 18 words 326.
+constexpr int kNlWords = 18;
+
+struct NlWave {
+    uint2 q[kNlWords + 1][64];  // queued (hit word, candidate of its bit 0), [position][lane]
+};
+
+// Offsets of a sheared system at its build step (zeros otherwise).
+struct LeNl {
+    double delta, dw;
+    uint32_t qd;
+};
+
+// Lanes' (lower half of a, lower half of b) and (upper half of a, upper half
+// of b): the two 32-particle blocks' operands from per-lane values.
+__device__ __forceinline__ void half_swap(uint32_t& a, uint32_t& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ void half_swap(float& a, float& b) {
+    uint32_t u = __float_as_uint(a), v = __float_as_uint(b);
+    half_swap(u, v);
+    a = __uint_as_float(u);
+    b = __uint_as_float(v);
+}
+
+// Bits e = 0..15 set where d[e] is negative.
+__device__ __forceinline__ uint32_t sign_bits(const f32x16& d) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int e = 15; e >= 0; --e) m = __builtin_amdgcn_alignbit(m, __float_as_uint(d[e]), 31);
+    return m;
+}
+
+// v0, v1 or v2 for a position below e0, below e1 or past it (by value: a
+// conditional over struct members selects an address and puts the struct in
+// scratch memory).
+__device__ __forceinline__ int pick(int k, int e0, int e1, int v0, int v1, int v2) {
+    const int v = k < e1 ? v1 : v2;
+    return k < e0 ? v0 : v;
+}
+
+template <bool LE>
+__device__ __forceinline__ void nl_mtile(const Geom& g, const Bufs& b, int64_t t, int parity, int bonded, NlWave& sh,
+                                         const LeNl& le, int& local_max, bool& overflow) {
+    const int lane = threadIdx.x & (kTile - 1);
+    const int64_t n = g.n, p0 = t * kTile;
+    const int self = (int)p0 + lane;
+    const int nv = n - p0 < kTile ? (int)(n - p0) : kTile;
+    const bool valid = lane < nv;
+    const double4* __restrict__ x = b.x[parity];
+    const char* __restrict__ xqb = reinterpret_cast<const char*>(b.xq[parity]);
+    const int32_t* __restrict__ cs = b.cstart;
+    const int kc = g.kc, nx = g.nc[0], cap = g.cap;
+    int cxl = -1, cyl = -1, czl = -1;
+    int4 qi = make_int4(0, 0, 0, 0);
+    if (valid) {
+        const double4 xi = x[self];
+        cell_coords(g, xi.x, xi.y, xi.z, cxl, cyl, czl);
+        qi = b.xq[parity][self];
+    }
+    char* const rowb = reinterpret_cast<char*>(b.nl + p0 * cap) + 4 * lane;
+    int cnt = 0;
+    // the candidate (of 64) a lane loads: matrix row 8 (e / 4) + 4 h + e % 4
+    // of a 32-candidate half comes back as bit 16 h + e of its hit word
+    const int ck = (lane & 32) + ((lane >> 2) & 1) * 16 + ((lane & 31) >> 3) * 4 + (lane & 3);
+    const float l0 = g.ql[0], l1 = g.ql[1], l2 = g.ql[2];
+    const int xlimit = min(nx - 2 * kc - 2, kNlSpan);
+    int lo = 0;
+    while (lo < nv) {
+        const int x0 = __builtin_amdgcn_readlane(cxl, lo);
+        const int y0 = __builtin_amdgcn_readlane(cyl, lo);
+        const int z0 = __builtin_amdgcn_readlane(czl, lo);
+        const int hi = lo + (int)__popcll(__ballot(valid && lane >= lo && cyl == y0 && czl == z0 && cxl <= x0 + xlimit));
+        const int x1 = __builtin_amdgcn_readlane(cxl, hi - 1);
+        const bool mine = lane >= lo && lane < hi;
+        // lane v: the first or second contiguous range of stencil row v / 2
+        // (rows z-major; empty when the row does not wrap)
+        const int side = 2 * kc + 1;
+        int pa = 0, pe = 0, psg = 0;
+        if (lane < 2 * side * side) {
+            const int r = lane >> 1, pc = lane & 1;
+            const int nz = wrapc(z0 + r / side - kc, g.nc[2]);
+            const int yraw = y0 + r % side - kc, ny = wrapc(yraw, g.nc[1]);
+            const int64_t rowc = ((int64_t)nz * g.nc[1] + ny) * nx;
+            int xa = x0 - kc, xb = x1 + kc;
+            if (LE) {
+                // across the y-boundary the x-range is re-centred by the
+                // offset, with one cell of margin each side
+                psg = yraw < 0 ? 1 : (yraw >= g.nc[1] ? -1 : 0);
+                if (psg != 0) {
+                    const double rv = sqrt(g.rv2), sd = psg * le.delta;
+                    xa = (int)floor((x0 * g.h[0] + sd - rv) * g.invh[0]) - 1;
+                    xb = (int)floor(((x1 + 1) * g.h[0] + sd + rv) * g.invh[0]) + 1;
+                }
+            }
+            if (LE && xb - xa + 1 >= nx) {
+                if (pc == 0) { pa = cs[rowc]; pe = cs[rowc + nx]; }
+            } else {
+                const int l = LE ? ((xa % nx) + nx) % nx : wrapc(xa, nx);
+                const int h = l + (xb - xa);
+                if (h < nx) {
+                    if (pc == 0) { pa = cs[rowc + l]; pe = cs[rowc + h + 1]; }
+                } else if (pc == 0) {
+                    pa = cs[rowc + l]; pe = cs[rowc + nx];
+                } else {
+                    pa = cs[rowc]; pe = cs[rowc + h - nx + 1];
+                }
+            }
+        }
+        uint64_t pm = __ballot(pe > pa);
+        // coordinates relative to the segment's centre, the particles' operands
+        const uint32_t ox = (uint32_t)__builtin_amdgcn_readfirstlane((int)quantize(0.5 * (x0 + x1 + 1) * g.h[0], g.qs[0]));
+        const uint32_t oy = (uint32_t)__builtin_amdgcn_readfirstlane((int)quantize((y0 + 0.5) * g.h[1], g.qs[1]));
+        const uint32_t oz = (uint32_t)__builtin_amdgcn_readfirstlane((int)quantize((z0 + 0.5) * g.h[2], g.qs[2]));
+        float bx0, bx1, bz0, bz1, c0, c1;
+        {
+            const float fx = qdiff((uint32_t)qi.x, ox, l0), fy = qdiff((uint32_t)qi.y, oy, l1),
+                        fz = qdiff((uint32_t)qi.z, oz, l2);
+            bx0 = -2.f * fx; bx1 = -2.f * fy;
+            half_swap(bx0, bx1);
+            bz0 = -2.f * fz; bz1 = 1.f;
+            half_swap(bz0, bz1);
+            c0 = c1 = fx * fx + fy * fy + fz * fz - (float)g.rv2;
+            half_swap(c0, c1);
+        }
+        f32x16 C0, C1;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { C0[e] = c0; C1[e] = c1; }
+        // Rounding bound of a result near the threshold, where every
+        // coordinate is within half the segment plus the stencil of the
+        // centre: with E the length of that corner vector, coordinates are
+        // within 2^-23 relative (8 units of 2^-24 E^2 in r^2), |r_i|^2 and
+        // |r_j|^2 within 3 units each, the accumulator's start within 1, the
+        // four products and sums within 24; 64 units, and the fixed-point
+        // band.
+        float delta;
+        {
+            const float ex = (0.5f * (float)(x1 - x0 + 1) + (float)kc) * (float)g.h[0];
+            const float ey = (0.5f + (float)kc) * (float)g.h[1], ez = (0.5f + (float)kc) * (float)g.h[2];
+            delta = 64.f * 0x1.0p-24f * (ex * ex + ey * ey + ez * ez) + (g.rv2hi - (float)g.rv2);
+        }
+        int qn = 0;         // words queued by this lane
+        // every lane writes its next hit, slot by slot; the word after the
+        // current one is read ahead, an empty word ends the queue
+        auto emit = [&]() __attribute__((always_inline)) {
+            sh.q[qn][lane] = make_uint2(0u, 0u);
+            __builtin_amdgcn_wave_barrier();
+            uint2 c = sh.q[0][lane];
+            int k = min(1, qn);
+            while (__any(c.x != 0)) {
+                const uint2 nx2 = sh.q[k][lane];
+                if (c.x != 0 && cnt < cap)
+                    *reinterpret_cast<int32_t*>(rowb + ((uint32_t)cnt << 8)) = (int)c.y + __ffs(c.x) - 1;
+                cnt += c.x != 0 ? 1 : 0;
+                c.x &= c.x - 1;
+                const bool done = c.x == 0;
+                c.x = done ? nx2.x : c.x;
+                c.y = done ? nx2.y : c.y;
+                k = min(k + (done ? 1 : 0), qn);
+            }
+            __builtin_amdgcn_wave_barrier();
+            qn = 0;
+        };
+        // candidate stream: up to 64 candidates of up to three ranges
+        int jc = 0, je = 0, sg = 0;
+        auto next_range = [&]() __attribute__((always_inline)) {
+            jc = je = 0;
+            if (pm) {
+                const int v = __ffsll((unsigned long long)pm) - 1;
+                pm &= pm - 1;
+                jc = __builtin_amdgcn_readlane(pa, v);
+                je = __builtin_amdgcn_readlane(pe, v);
+                if (LE) sg = __builtin_amdgcn_readlane(psg, v);
+            }
+        };
+        // parts 0, 1, 2: end among the chunk's candidates (e), sorted index
+        // minus position (j), sheared image (s)
+        struct Chunk {
+            int e0, e1, e2, j0, j1, j2, s0, s1, s2;
+        };
+        auto part = [&](int& pos, int& e, int& j, int& s) __attribute__((always_inline)) {
+            const int m = min(64 - pos, je - jc);
+            j = jc - pos;
+            s = sg;
+            pos += m;
+            e = pos;
+            jc += m;
+            if (jc == je) next_range();
+        };
+        auto take = [&]() __attribute__((always_inline)) {
+            Chunk c;
+            int pos = 0;
+            part(pos, c.e0, c.j0, c.s0);
+            part(pos, c.e1, c.j1, c.s1);
+            part(pos, c.e2, c.j2, c.s2);
+            return c;
+        };
+        auto load = [&](const Chunk& c) __attribute__((always_inline)) {
+            const int k = min(ck, max(c.e2 - 1, 0));
+            const int j = k + pick(k, c.e0, c.e1, c.j0, c.j1, c.j2);
+            int4 q = *reinterpret_cast<const int4*>(xqb + ((uint32_t)j << 4));
+            if (LE) {
+                const int sj = pick(k, c.e0, c.e1, c.s0, c.s1, c.s2);
+                q.x = (int)((uint32_t)q.x - (uint32_t)(sj * (int64_t)le.qd));
+            }
+            return q;
+        };
+        next_range();
+        Chunk c = take();
+        int4 rec = load(c);
+        while (c.e2 > 0) {
+            const Chunk cn = take();
+            const int4 recn = load(cn);
+            float fx = qdiff((uint32_t)rec.x, ox, l0), fy = qdiff((uint32_t)rec.y, oy, l1),
+                  fz = qdiff((uint32_t)rec.z, oz, l2);
+            float nj = fx * fx + fy * fy + fz * fz;
+            // the operands of candidates 0..31 (fx, fz) and 32..63 (fy, nj)
+            half_swap(fx, fy);
+            half_swap(fz, nj);
+#pragma unroll 1
+            for (int h0 = 0; h0 < c.e2; h0 += 32) {
+                f32x16 D0 = __builtin_amdgcn_mfma_f32_32x32x2f32(fx, bx0, C0, 0, 0, 0);
+                f32x16 D1 = __builtin_amdgcn_mfma_f32_32x32x2f32(fx, bx1, C1, 0, 0, 0);
+                D0 = __builtin_amdgcn_mfma_f32_32x32x2f32(fz, bz0, D0, 0, 0, 0);
+                D1 = __builtin_amdgcn_mfma_f32_32x32x2f32(fz, bz1, D1, 0, 0, 0);
+                fx = fy;
+                fz = nj;
+                uint32_t m = sign_bits(D0), mh = sign_bits(D1);
+                half_swap(m, mh);
+                m |= mh << 16;
+                float near = 3.0e38f;
+#pragma unroll
+                for (int e = 0; e < 16; e += 2) {
+                    near = fminf(fminf(fabsf(D0[e]), fabsf(D0[e + 1])), near);
+                    near = fminf(fminf(fabsf(D1[e]), fabsf(D1[e + 1])), near);
+                }
+                if (__builtin_expect(__any(near <= delta), 0)) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        D0[e] = fabsf(D0[e]) <= delta ? -1.f : 1.f;
+                        D1[e] = fabsf(D1[e]) <= delta ? -1.f : 1.f;
+                    }
+                    uint32_t bd = sign_bits(D0), bh = sign_bits(D1);
+                    half_swap(bd, bh);
+                    bd |= bh << 16;
+                    const int nval = c.e2 - h0;
+                    if (nval < 32) bd &= (1u << nval) - 1u;
+                    if (!mine) bd = 0;
+                    if (bd) {
+                        const double4 xi = x[self];
+                        while (bd) {
+                            const int bit = __ffs(bd) - 1, k = bit + h0;
+                            bd &= bd - 1;
+                            const double4 xj = x[k + pick(k, c.e0, c.e1, c.j0, c.j1, c.j2)];
+                            const bool in = (LE ? exact_r2_le(g, xi, xj, le.dw) : exact_r2(g, xi, xj)) < g.rv2;
+                            m = (m & ~(1u << bit)) | ((in ? 1u : 0u) << bit);
+                        }
+                    }
+                }
+                if (!mine) m = 0;
+                // the hits of each range, without the particle itself
+                int from = 0, to = c.e0, j = c.j0;
+#pragma unroll 1
+                for (int q = 0; q < 3; ++q) {
+                    const int b0 = max(from - h0, 0), b1 = min(to - h0, 32);
+                    if (b1 > b0) {
+                        const int jb = j + h0;
+                        uint32_t mq = m & ((0xffffffffu >> (32 - (b1 - b0))) << b0);
+                        if (jb + b0 < (int)p0 + kTile && jb + b1 > (int)p0) {
+                            const uint32_t sb = (uint32_t)(self - jb);
+                            if (sb < 32u) mq &= ~(1u << sb);
+                        }
+                        sh.q[qn][lane] = make_uint2(mq, (uint32_t)jb);
+                        qn += mq ? 1 : 0;
+                        if (__any(qn == kNlWords)) emit();
+                    }
+                    from = to;
+                    to = pick(q, 1, 2, c.e1, c.e2, c.e2);
+                    j = pick(q, 1, 2, c.j1, c.j2, c.j2);
+                }
+            }
+            c = cn;
+            rec = recn;
+        }
+        emit();
+        lo = hi;
+    }
+    if (valid) {
+        b.ncount[self] = cnt;
+        if (cnt > local_max) local_max = cnt;
+        if (cnt > cap) overflow = true;
+        // padding to a multiple of 8 with the particle itself (as nl_one)
+        for (int k = cnt; k < ((cnt + 7) & ~7) && k < cap; ++k)
+            *reinterpret_cast<int32_t*>(rowb + ((uint32_t)k << 8)) = self;
+        if (bonded) remap_bonded(b, n, self);
+    }
+}
+
+// One wavefront per block and a few tiles in turn for each: the tiles' times
+// differ by what their segments are, and wavefronts that share a block would
+// hold its LDS until the last is done.
+constexpr int kNlGrid = 8192;
+template <bool LE>
+__global__ void __launch_bounds__(kTile) k_nl_mtile(Geom g, Bufs b, int parity, int bonded) {
+    __shared__ NlWave sh;
+    if (!rebuild_requested(b)) return;
+    LeNl le{0.0, 0.0, 0u};
+    if (LE) {
+        le.delta = le_delta(g, b.ctl->step);
+        le.dw = le_fold(g, le.delta);
+        le.qd = quantize(le.delta, g.qs[0]);
+    }
+    int local_max = 0;
+    bool overflow = false;
+    const int64_t nt = (g.n + kTile - 1) / kTile, blk = xcd_block(blockIdx.x, gridDim.x);
+    for (int64_t t = blk * nt / gridDim.x; t < (blk + 1) * nt / gridDim.x; ++t)
+        nl_mtile<LE>(g, b, t, parity, bonded, sh, le, local_max, overflow);
     nl_epilogue(b, local_max, overflow);
 }
 
@@ -2397,23 +2532,33 @@ __global__ void __launch_bounds__(kBlock) k_batch_commit(const SysEntry* __restr
     if (r.i < g.n) commit_one(g, b, r.i, parity, r.e->bonded);
 }
 
+// Members whose list is built one particle per lane.
 __global__ void __launch_bounds__(kBlock) k_batch_nl(const SysEntry* __restrict__ tab,
                                                      const int32_t* __restrict__ tile_sys, int parity) {
     const TileRef r = tile_ref_spread(tab, tile_sys);
     const Bufs& b = r.e->a.b;
-    if (!rebuild_requested(b)) return;
     const Geom& g = r.e->a.g;
+    if (g.nl_mat || !rebuild_requested(b)) return;
     int local_max = 0;
     bool overflow = false;
-    if (g.nl_tile) {
-        const int64_t t = r.lt * (kBlock / kTile) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kTile));
-        if (t * kTile < g.n) {
-            if (g.nl_cubic) nl_tile<true>(g, b, t, parity, r.e->bonded, local_max, overflow);
-            else nl_tile<false>(g, b, t, parity, r.e->bonded, local_max, overflow);
-        }
-    } else if (r.i < g.n) {
-        nl_one(g, b, r.i, parity, r.e->bonded, local_max, overflow);
-    }
+    if (r.i < g.n) nl_one(g, b, r.i, parity, r.e->bonded, local_max, overflow);
+    nl_epilogue(b, local_max, overflow);
+}
+
+// Members whose list is built on the matrix cores: one wavefront per
+// 64-particle tile, four to a tile of the batch.
+__global__ void __launch_bounds__(kTile) k_batch_nl_mtile(const SysEntry* __restrict__ tab,
+                                                          const int32_t* __restrict__ tile_sys, int parity) {
+    __shared__ NlWave sh;
+    const SysEntry* e = tab + tile_sys[blockIdx.x / (kBlock / kTile)];
+    const Bufs& b = e->a.b;
+    const Geom& g = e->a.g;
+    if (!g.nl_mat || !rebuild_requested(b)) return;
+    const int64_t t = (int64_t)blockIdx.x - e->tile0 * (kBlock / kTile);
+    if (t * kTile >= g.n) return;
+    int local_max = 0;
+    bool overflow = false;
+    nl_mtile<false>(g, b, t, parity, e->bonded, sh, LeNl{0.0, 0.0, 0u}, local_max, overflow);
     nl_epilogue(b, local_max, overflow);
 }
 
@@ -2527,11 +2672,14 @@ hipError_t launch_rebuild(const Geom& g, const Bufs& b, int parity, int bonded, 
     hipLaunchKernelGGL(k_rank_permute, dim3(gs), dim3(kBlock), 0, s, g, b, parity);
     hipLaunchKernelGGL(k_commit, dim3(gs), dim3(kBlock), 0, s, g, b, parity, bonded);
     if (ev_sorted) (void)hipEventRecord(ev_sorted, s);
-    if (g.le)
+    const int64_t nt = (g.n + kTile - 1) / kTile;
+    const dim3 tiles((unsigned)(nt < kNlGrid ? nt : kNlGrid));
+    if (g.nl_mat && g.le)
+        hipLaunchKernelGGL(k_nl_mtile<true>, tiles, dim3(kTile), 0, s, g, b, parity, bonded);
+    else if (g.nl_mat)
+        hipLaunchKernelGGL(k_nl_mtile<false>, tiles, dim3(kTile), 0, s, g, b, parity, bonded);
+    else if (g.le)
         hipLaunchKernelGGL(k_nl_build_le, dim3(grid_for(g.n, 1 << 20)), dim3(kBlock), 0, s, g, b, parity, bonded);
-    else if (g.nl_tile)
-        hipLaunchKernelGGL(k_nl_tiles, dim3((unsigned)((g.n + kNlBlock - 1) / kNlBlock)), dim3(kNlBlock), 0, s, g, b,
-                           parity, bonded);
     else
         hipLaunchKernelGGL(k_nl_build, dim3(grid_for(g.n, 1 << 20)), dim3(kBlock), 0, s, g, b, parity, bonded);
     return hipGetLastError();
@@ -2657,7 +2805,10 @@ hipError_t launch_batch_rebuild(const BatchCells& bc, const SysEntry* tab, const
     hipLaunchKernelGGL(k_batch_permute, tg, blk, 0, s, tab, tile_sys, parity);
     hipLaunchKernelGGL(k_batch_commit, tg, blk, 0, s, tab, tile_sys, parity);
     if (ev_sorted) (void)hipEventRecord(ev_sorted, s);
-    hipLaunchKernelGGL(k_batch_nl, tg, blk, 0, s, tab, tile_sys, parity);
+    if (bc.any_mat)
+        hipLaunchKernelGGL(k_batch_nl_mtile, dim3((unsigned)ntiles * (kBlock / kTile)), dim3(kTile), 0, s, tab, tile_sys,
+                           parity);
+    if (bc.any_one) hipLaunchKernelGGL(k_batch_nl, tg, blk, 0, s, tab, tile_sys, parity);
     return hipGetLastError();
 }
 
