@@ -559,52 +559,73 @@ static int block_of(md_handle h) { return h->cfg.block_size ? h->cfg.block_size 
 // gradients passed on as BF16 rows.  FP32 form: descriptor rows, then the
 // FP32 network.  *spart receives the network's energy partials (one row),
 // or nullptr.
-static hipError_t launch_force_stage(md_handle h, int mode, int tensor, double* f_out, const double** spart) {
+// defer: the previous step's record is written by this stage's step kernel.
+static hipError_t launch_force_stage(md_handle h, int mode, int tensor, double* f_out, const double** spart,
+                                     int defer = 0) {
     StepArgs a = make_args(h, mode, tensor, f_out);
+    a.fin = defer;
     *spart = nullptr;
     if (h->pair_mode == MD_PAIR_PLAIN)
         return launch_step(a, h->fp64, h->single, h->bonded, block_of(h), h->stream);
     hipError_t e;
     const SurBufs& s = h->sb;
     const int bf = h->sur_prec == MD_SUR_BF16;
+    // energy partials by parity, as the step kernel's own
+    double* const epart = s.part + (int64_t)h->parity * h->step_grid;
+    if (defer) a.fin_spart = s.part + (int64_t)(h->parity ^ 1) * h->step_grid;
     if (bf) {
-        if ((e = launch_sur_desc2(h->g, h->b, s, h->sc, h->parity, 1, h->stream)) != hipSuccess) return e;
+        if ((e = launch_sur_desc2(h->g, h->b, s, h->sc, h->parity, 1, h->stream, epart)) != hipSuccess) return e;
     } else {
         if ((e = launch_sur_desc2(h->g, h->b, s, h->sc, h->parity, 0, h->stream)) != hipSuccess) return e;
-        if ((e = launch_sur_mlp(s, s.G, h->g.n, s.a, nullptr, s.part, 0, h->step_grid, h->stream)) != hipSuccess)
+        if ((e = launch_sur_mlp(s, s.G, h->g.n, s.a, nullptr, epart, 0, h->step_grid, h->stream)) != hipSuccess)
             return e;
     }
-    *spart = s.part;
+    *spart = epart;
     return launch_sur_step(a, s, h->sc, h->bonded, bf, h->stream);
 }
 
 // the finalize of a force stage: surrogate partials carry the energy only;
 // the plain kernels leave one partial column per block they ran
-static hipError_t launch_stage_finalize(md_handle h, int mode, const double* spart, int tensor) {
-    int nb = h->step_grid;
-    if (h->pair_mode == MD_PAIR_PLAIN) nb = step_launch_grid(make_args(h, mode, tensor, nullptr), h->fp64, block_of(h));
-    return launch_finalize(h->b, nb, mode, spart, tensor, h->stream, 1);
+static hipError_t launch_stage_finalize(md_handle h, int parity, int mode, const double* spart, int tensor) {
+    int nb = h->step_grid, block = kBlock;
+    if (h->pair_mode == MD_PAIR_PLAIN) {
+        const StepArgs a = make_args(h, mode, tensor, nullptr);
+        nb = step_launch_grid(a, h->fp64, block_of(h));
+        if (!a.dy.gen && !h->fp64 && a.use_fast) block = block_of(h);
+    }
+    return launch_finalize(h->b, parity, nb, block, mode, spart, tensor, h->stream, 1);
+}
+
+// A step's record is left to the next step's kernel, and to finish_steps at the
+// end of the call, unless its sums take the partials' every row (the tensor)
+// or each stage is timed by itself.
+static bool defer_records(md_handle h) { return !(h->cfg.flags & MD_CFG_VIRIAL_TENSOR) && !h->timing; }
+
+static hipError_t finish_steps(md_handle h) {
+    const int p = h->parity ^ 1;    // of the last step
+    const double* spart = h->pair_mode == MD_PAIR_PLAIN ? nullptr : h->sb.part + (int64_t)p * h->step_grid;
+    return launch_stage_finalize(h, p, MODE_STEP, spart, (h->cfg.flags & MD_CFG_VIRIAL_TENSOR) ? 1 : 0);
 }
 
 // Enqueue one full step at the handle's current parity and advance the
 // host mirrors.  Events (timing mode) bracket the three stages.
 static hipError_t enqueue_step(md_handle h, const EvQuad* q) {
     hipError_t e;
+    const int defer = defer_records(h) ? 1 : 0;
     if (q) (void)hipEventRecord(q->e[0], h->stream);
-    e = launch_rebuild(h->g, h->b, h->parity, h->bonded, h->stream, q ? q->e[4] : nullptr);
+    e = launch_rebuild(h->g, h->b, h->parity, h->bonded, 1, h->stream, q ? q->e[4] : nullptr);
     if (e != hipSuccess) return e;
     if (q) (void)hipEventRecord(q->e[1], h->stream);
     const double* spart = nullptr;
     const int tensor = (h->cfg.flags & MD_CFG_VIRIAL_TENSOR) ? 1 : 0;
-    e = launch_force_stage(h, MODE_STEP, tensor, nullptr, &spart);
+    e = launch_force_stage(h, MODE_STEP, tensor, nullptr, &spart, defer);
     if (e != hipSuccess) return e;
     if (q) (void)hipEventRecord(q->e[2], h->stream);
-    e = launch_stage_finalize(h, MODE_STEP, spart, tensor);
-    if (e != hipSuccess) return e;
-    if (q) (void)hipEventRecord(q->e[3], h->stream);
     h->parity ^= 1;
     h->host_step += 1;
     h->vel_half = 1;
+    if (!defer && (e = finish_steps(h)) != hipSuccess) return e;
+    if (q) (void)hipEventRecord(q->e[3], h->stream);
     return hipSuccess;
 }
 
@@ -637,7 +658,7 @@ static md_status build_graph(md_handle h) {
 
 static md_status rebuild_now(md_handle h, int force) {
     if (force) HIP_TRY(h, launch_set_ctl(h->b, -1, -1, 1, 0, h->stream));
-    HIP_TRY(h, launch_rebuild(h->g, h->b, h->parity, h->bonded, h->stream));
+    HIP_TRY(h, launch_rebuild(h->g, h->b, h->parity, h->bonded, 0, h->stream));
     HIP_TRY(h, launch_clear_rebuild(h->b, h->stream));
     return MD_OK;
 }
@@ -1052,7 +1073,7 @@ md_status md_forces(md_handle h, double* f_out) {
     if (r != MD_OK) return r;
     const double* spart = nullptr;
     HIP_TRY(h, launch_force_stage(h, MODE_FORCES, 1, f_out, &spart));
-    HIP_TRY(h, launch_stage_finalize(h, MODE_FORCES, spart, 1));
+    HIP_TRY(h, launch_stage_finalize(h, h->parity, MODE_FORCES, spart, 1));
     return MD_OK;
 }
 
@@ -1096,6 +1117,7 @@ md_status md_step(md_handle h, int64_t nsteps) {
         HIP_TRY(h, enqueue_step(h, qp));
         --left;
     }
+    if (nsteps > 0 && defer_records(h)) HIP_TRY(h, finish_steps(h));
     return MD_OK;
 }
 
@@ -1106,7 +1128,7 @@ md_status md_observables(md_handle h, md_obs* out) {
     if (r != MD_OK) return r;
     const double* spart = nullptr;
     HIP_TRY(h, launch_force_stage(h, MODE_OBSERVE, 1, nullptr, &spart));
-    HIP_TRY(h, launch_stage_finalize(h, MODE_OBSERVE, spart, 1));
+    HIP_TRY(h, launch_stage_finalize(h, h->parity, MODE_OBSERVE, spart, 1));
     double rec[kHistRec];
     HIP_TRY(h, hipMemcpyAsync(rec, h->b.cur, sizeof(rec), hipMemcpyDeviceToHost, h->stream));
     DevCtl c;
@@ -1507,15 +1529,16 @@ md_status bfail(md_batch b, md_status st, const std::string& msg) {
 
 hipError_t batch_enqueue_step(md_batch b, const EvQuad* q = nullptr) {
     if (q) (void)hipEventRecord(q->e[0], b->stream);
-    hipError_t e = launch_batch_rebuild(b->bc, b->tabs[0][b->parity], b->tile_sys, b->ntiles, b->parity, b->stream,
+    const int defer = b->timing ? 0 : 1;
+    SysEntry* const tab = b->tabs[0][b->parity];
+    hipError_t e = launch_batch_rebuild(b->bc, tab, b->tile_sys, b->ntiles, b->parity, 1, b->stream,
                                         q ? q->e[4] : nullptr);
     if (e != hipSuccess) return e;
     if (q) (void)hipEventRecord(q->e[1], b->stream);
-    e = launch_batch_step(b->tabs[0][b->parity], b->tile_sys, b->ntiles, b->parity, MODE_STEP, 0, b->stream);
+    e = launch_batch_step(tab, b->tile_sys, b->ntiles, b->nsys, defer, 0, b->stream);
     if (e != hipSuccess) return e;
     if (q) (void)hipEventRecord(q->e[2], b->stream);
-    e = launch_batch_finalize(b->tabs[0][b->parity], b->nsys, MODE_STEP, b->stream);
-    if (e != hipSuccess) return e;
+    if (!defer && (e = launch_batch_finalize(tab, b->nsys, MODE_STEP, b->stream)) != hipSuccess) return e;
     if (q) (void)hipEventRecord(q->e[3], b->stream);
     b->parity ^= 1;
     b->host_step += 1;
@@ -1708,6 +1731,9 @@ md_status md_batch_step(md_batch b, int64_t nsteps) {
         BHIP_TRY(b, batch_enqueue_step(b));
         --left;
     }
+    // the last step's records (the others were written by the steps after them)
+    if (nsteps > 0 && !b->timing)
+        BHIP_TRY(b, launch_batch_finalize(b->tabs[0][b->parity ^ 1], b->nsys, MODE_STEP, b->stream));
     batch_sync_members(b);
     return MD_OK;
 }
@@ -1715,8 +1741,8 @@ md_status md_batch_step(md_batch b, int64_t nsteps) {
 md_status md_batch_observables(md_batch b, md_obs* out) {
     if (!b || !out) return fail(nullptr, MD_ERR_ARG, "NULL argument");
     SysEntry* to = b->tabs[1][b->parity];
-    BHIP_TRY(b, launch_batch_rebuild(b->bc, to, b->tile_sys, b->ntiles, b->parity, b->stream));
-    BHIP_TRY(b, launch_batch_step(to, b->tile_sys, b->ntiles, b->parity, MODE_OBSERVE, 1, b->stream));
+    BHIP_TRY(b, launch_batch_rebuild(b->bc, to, b->tile_sys, b->ntiles, b->parity, 0, b->stream));
+    BHIP_TRY(b, launch_batch_step(to, b->tile_sys, b->ntiles, b->nsys, 0, 1, b->stream));
     BHIP_TRY(b, launch_batch_finalize(to, b->nsys, MODE_OBSERVE, b->stream));
     BHIP_TRY(b, launch_batch_gather_obs(to, b->nsys, b->obs, b->stream));
     std::vector<double> rec((size_t)kHistRec * b->nsys);

@@ -27,14 +27,22 @@ enum Hist { H_STEP = 0, H_EPAIR, H_EBOND, H_EANGLE, H_EKIN, H_VIR, H_T0, H_NREB 
 struct DevCtl {
     int64_t step;          // n of the positions x_n currently stored
     int32_t vel_half;      // 1: stored velocity is v_{n-1/2}; 0: on-step v_n
-    uint32_t rebuild;      // rebuild the list before the next force evaluation
-    uint32_t rebuild_next; // set by the step kernel when a particle moved > skin/2
+    uint32_t rebuild[2];   // by position parity: rebuild the list before the next force
+                           // evaluation.  The step kernel of one parity sets the other's
+                           // flag when a particle moved > skin/2
     uint32_t status;       // sticky MD_FLAG_* bits
     int32_t nl_max;        // longest row at the last build
     int32_t pad0;
     int64_t n_rebuilds;
     int64_t build_step;    // step of the positions the list was last built from
-    int64_t pad[10];
+    // A step's record is written (and the counter advanced) by the next step of
+    // the same call, or by the finalize kernel that ends the call
+    int32_t ran;           // a step has run since the counter was last advanced
+    int32_t fin_prev;      // the current step kernel writes the previous step's record
+    uint32_t prev_status;  // status, longest row and rebuild count at that step's end
+    int32_t prev_nl_max;
+    int64_t prev_rebuilds;
+    int64_t pad[7];
 };
 
 // One type pair, precomputed on the host in FP64 and rounded once for FP32.
@@ -111,7 +119,7 @@ struct Geom {
 
 struct Bufs {
     DevCtl* ctl;
-    double* partials;       // [kNacc][grid]
+    double* partials;       // [kNacc][grid]; without the tensor rows 0..4 and 5..9 by parity
     double* hist;           // [MD_HISTORY_CAPACITY][kHistRec]
     double* cur;            // [kHistRec] observables of the last finalize
     double4* x[2];          // positions (w = type), sorted order, by step parity
@@ -178,7 +186,8 @@ struct Dyn {
 // internal status bit (init only): a particle type outside 0..n_types-1
 constexpr uint32_t MD_FLAG_BAD_TYPE = 0x100u;
 
-enum Mode { MODE_STEP = 0, MODE_OBSERVE = 1, MODE_FORCES = 2 };
+// MODE_PREV: finalize only, the step before the one a step kernel is running
+enum Mode { MODE_STEP = 0, MODE_OBSERVE = 1, MODE_FORCES = 2, MODE_PREV = 3 };
 
 // Single-type LJ coefficients rescaled to fixed-point length units u = L/2^32
 // (cubic box): r2 and the band limits in u^2, sigma^2 / u^2, 24 eps / u.
@@ -201,6 +210,8 @@ struct StepArgs {
     int32_t mode;
     int32_t tensor;
     double* f_out;              // MODE_FORCES: [N][3] tag order
+    int32_t fin;                // 1: block 0 of the grid writes the previous step's record
+    const double* fin_spart;    // that step's surrogate energy partials, or null
 };
 
 // ------------------------------------------------------------------ surrogate
@@ -288,7 +299,7 @@ hipError_t launch_sur_f_to_tag(const Geom& g, const Bufs& b, const float4* src, 
 // network on given rows, and the pair force fused with bonded forces and
 // integration (the step kernel of the surrogate mode)
 hipError_t launch_sur_desc2(const Geom& g, const Bufs& b, const SurBufs& s, const SurConst& c, int parity, int net,
-                            hipStream_t st);
+                            hipStream_t st, double* epart = nullptr);
 hipError_t launch_sur_mlp16(const SurBufs& s, const float* G, int64_t P, float* a, float* e, hipStream_t st);
 hipError_t launch_sur_step(const StepArgs& a, const SurBufs& s, const SurConst& c, int bonded, int a_bf16,
                            hipStream_t st);
@@ -318,8 +329,9 @@ struct BatchCells {
 
 // ev_sorted (or null) is recorded between the cell sort and the list build
 hipError_t launch_batch_rebuild(const BatchCells& bc, const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles,
-                                int parity, hipStream_t s, hipEvent_t ev_sorted = nullptr);
-hipError_t launch_batch_step(const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles, int parity, int mode,
+                                int parity, int advance, hipStream_t s, hipEvent_t ev_sorted = nullptr);
+// fin: the launch also writes every member's previous step's record
+hipError_t launch_batch_step(const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles, int nsys, int fin,
                              int tensor, hipStream_t s);
 hipError_t launch_batch_finalize(const SysEntry* tab, int nsys, int mode, hipStream_t s);
 hipError_t launch_batch_gather_obs(const SysEntry* tab, int nsys, double* out, hipStream_t s);
@@ -330,7 +342,8 @@ hipError_t launch_init_load(const Geom& g, const Bufs& b, int parity, const doub
                             hipStream_t s);
 hipError_t launch_set_ctl(const Bufs& b, int64_t step, int vel_half, int rebuild, int clear_status,
                           hipStream_t s);
-hipError_t launch_rebuild(const Geom& g, const Bufs& b, int parity, int bonded, hipStream_t s,
+// advance: the stage belongs to a step (the step counter moves past the last one)
+hipError_t launch_rebuild(const Geom& g, const Bufs& b, int parity, int bonded, int advance, hipStream_t s,
                           hipEvent_t ev_sorted = nullptr);
 hipError_t launch_clear_rebuild(const Bufs& b, hipStream_t s);
 hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded, int block,
@@ -341,8 +354,9 @@ int step_grid(int64_t n);
 int step_launch_grid(const StepArgs& a, int fp64, int block);
 // spart: surrogate partials (row 0 energy; with spart_rows 8 also virial and
 // tensor rows), or nullptr
-hipError_t launch_finalize(const Bufs& b, int nblocks, int mode, const double* spart, int tensor, hipStream_t s,
-                           int spart_rows = 8);
+// block: threads of the step kernel's blocks; parity: of the step finalized
+hipError_t launch_finalize(const Bufs& b, int parity, int nblocks, int block, int mode, const double* spart,
+                           int tensor, hipStream_t s, int spart_rows = 8);
 hipError_t launch_overwrite_state(const Geom& g, const Bufs& b, int parity, const double* pos,
                                   const double* vel, const int32_t* image, hipStream_t s);
 hipError_t launch_get_state(const Geom& g, const Bufs& b, int parity, double* pos, double* vel,

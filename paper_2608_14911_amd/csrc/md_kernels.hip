@@ -139,8 +139,28 @@ __device__ __forceinline__ const PairCoef<float>& coef<float>(const PairTable& p
 template <>
 __device__ __forceinline__ const PairCoef<double>& coef<double>(const PairTable& pt, int tp) { return pt.d[tp]; }
 
-__device__ __forceinline__ bool rebuild_requested(const Bufs& b) {
-    return __atomic_load_n(&b.ctl->rebuild, __ATOMIC_RELAXED) != 0;
+__device__ __forceinline__ bool rebuild_requested(const Bufs& b, int parity) {
+    return __atomic_load_n(&b.ctl->rebuild[parity], __ATOMIC_RELAXED) != 0;
+}
+
+// Start of a step, by one thread of the rebuild stage's first kernel: the step
+// that ran before it (if its call has not been finalized) ends here; its
+// record is left to the step kernel's first block (finalize_body, MODE_PREV),
+// where it costs no launch of its own.  The other parity's flag, last read by
+// the step before, is cleared for this step's kernel to set.
+__device__ __forceinline__ void advance_step(const Bufs& b, int parity) {
+    DevCtl* c = b.ctl;
+    const int ran = c->ran;
+    c->fin_prev = ran;
+    if (ran) {
+        c->prev_status = c->status;
+        c->prev_nl_max = c->nl_max;
+        c->prev_rebuilds = c->n_rebuilds;
+        c->step += 1;
+        c->vel_half = 1;
+    }
+    c->ran = 1;
+    c->rebuild[parity ^ 1] = 0;
 }
 
 // ------------------------------------------------------------------ init / state I/O
@@ -237,8 +257,8 @@ __global__ void k_set_ctl(Bufs b, int64_t step, int vel_half, int rebuild, int c
         DevCtl* c = b.ctl;
         if (step >= 0) c->step = step;
         if (vel_half >= 0) c->vel_half = vel_half;
-        if (rebuild >= 0) c->rebuild = (uint32_t)rebuild;
-        c->rebuild_next = 0;
+        if (rebuild >= 0) c->rebuild[0] = c->rebuild[1] = (uint32_t)rebuild;
+        c->ran = c->fin_prev = 0;
         if (clear_status) { c->status = 0; c->nl_max = 0; }
     }
 }
@@ -293,8 +313,9 @@ __device__ __forceinline__ int64_t scan_chunk_cells(const Geom& g) {
     return (g.ncell + kScanBlocks - 1) / kScanBlocks;
 }
 
-__global__ void __launch_bounds__(kBlock) k_bin(Geom g, Bufs b, int parity) {
-    if (!rebuild_requested(b)) return;
+__global__ void __launch_bounds__(kBlock) k_bin(Geom g, Bufs b, int parity, int advance) {
+    if (advance && gtid() == 0) advance_step(b, parity);
+    if (!rebuild_requested(b, parity)) return;
     const int64_t chunk = scan_chunk_cells(g);
     for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < g.n; i0 += gstride()) {
         const int64_t i = i0 + threadIdx.x;
@@ -338,7 +359,7 @@ __device__ __forceinline__ void scan_chunk(const Geom& g, int blk, int64_t& lo, 
 }
 
 __global__ void __launch_bounds__(kBlock) k_scan_reduce(Geom g, Bufs b) {
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, 0)) return;
     int64_t lo, hi;
     scan_chunk(g, blockIdx.x, lo, hi);
     int s = 0;
@@ -355,7 +376,7 @@ __global__ void __launch_bounds__(kBlock) k_scan_reduce(Geom g, Bufs b) {
 
 // Exclusive scan of the kScanBlocks chunk sums by one block.
 __global__ void __launch_bounds__(kScanBlocks) k_scan_top(Bufs b) {
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, 0)) return;
     __shared__ int wsum[kScanBlocks / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int v = b.bsum[threadIdx.x];
@@ -398,15 +419,15 @@ __device__ __forceinline__ void scan_apply_body(const Geom& g, const Bufs& b, in
 
 // Batches: chunk offsets from k_scan_reduce and k_scan_top.
 __global__ void __launch_bounds__(kBlock) k_scan_apply(Geom g, Bufs b) {
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, 0)) return;
     scan_apply_body(g, b, b.bsum[blockIdx.x]);
 }
 
 // One system: the chunk sums come from k_bin, and each block adds up the
 // sums of the chunks before its own (at most kScanBlocks values, read from
 // the L2), which replaces the reduction and top-level scan kernels.
-__global__ void __launch_bounds__(kBlock) k_scan_chunks(Geom g, Bufs b) {
-    if (!rebuild_requested(b)) return;
+__global__ void __launch_bounds__(kBlock) k_scan_chunks(Geom g, Bufs b, int parity) {
+    if (!rebuild_requested(b, parity)) return;
     int part = 0;
     for (int k = threadIdx.x; k < (int)blockIdx.x; k += kBlock) part += b.bsum[k * kChunkPad];
     int off;
@@ -433,8 +454,8 @@ __device__ __forceinline__ void scatter_one(const Bufs& b, int64_t i, bool activ
     }
 }
 
-__global__ void __launch_bounds__(kBlock) k_scatter(Geom g, Bufs b) {
-    if (!rebuild_requested(b)) return;
+__global__ void __launch_bounds__(kBlock) k_scatter(Geom g, Bufs b, int parity) {
+    if (!rebuild_requested(b, parity)) return;
     // the chunk sums were read by the scan: clear them for the next build
     for (int64_t k = gtid(); k < kScanBlocks; k += gstride()) b.bsum[k * kChunkPad] = 0;
     for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < g.n; i0 += gstride()) {
@@ -482,7 +503,7 @@ __device__ __forceinline__ void permute_one(const Geom& g, const Bufs& b, int64_
 }
 
 __global__ void __launch_bounds__(kBlock) k_rank_permute(Geom g, Bufs b, int parity) {
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, parity)) return;
     for (int64_t s = gtid(); s < g.n; s += gstride()) permute_one(g, b, s, parity);
 }
 
@@ -521,7 +542,7 @@ __device__ __forceinline__ void commit_one(const Geom& g, const Bufs& b, int64_t
 }
 
 __global__ void __launch_bounds__(kBlock) k_commit(Geom g, Bufs b, int parity, int bonded) {
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, parity)) return;
     for (int64_t s = gtid(); s < g.n; s += gstride()) commit_one(g, b, s, parity, bonded);
 }
 
@@ -743,7 +764,7 @@ __device__ __forceinline__ void nl_epilogue(const Bufs& b, int local_max, bool o
 }
 
 __global__ void __launch_bounds__(kBlock) k_nl_build(Geom g, Bufs b, int parity, int bonded) {
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, parity)) return;
     int local_max = 0;
     bool overflow = false;
     for (int64_t i = gtid_xcd(); i < g.n; i += gstride()) nl_one(g, b, i, parity, bonded, local_max, overflow);
@@ -919,7 +940,7 @@ __device__ __forceinline__ void nl_one_le(const Geom& g, const Bufs& b, int64_t 
 }
 
 __global__ void __launch_bounds__(kBlock) k_nl_build_le(Geom g, Bufs b, int parity, int bonded) {
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, parity)) return;
     const double delta = le_delta(g, b.ctl->step);
     const double dw = le_fold(g, delta);
     const uint32_t qd = quantize(delta, g.qs[0]);
@@ -1273,7 +1294,7 @@ constexpr int kNlGrid = 8192;
 template <bool LE>
 __global__ void __launch_bounds__(kTile) k_nl_mtile(Geom g, Bufs b, int parity, int bonded) {
     __shared__ NlWave sh;
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, parity)) return;
     LeNl le{0.0, 0.0, 0u};
     if (LE) {
         le.delta = le_delta(g, b.ctl->step);
@@ -1289,7 +1310,7 @@ __global__ void __launch_bounds__(kTile) k_nl_mtile(Geom g, Bufs b, int parity, 
 }
 
 __global__ void k_clear_rebuild(Bufs b) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) b.ctl->rebuild = 0;
+    if (threadIdx.x == 0 && blockIdx.x == 0) b.ctl->rebuild[0] = b.ctl->rebuild[1] = 0;
 }
 
 // ------------------------------------------------------------------ bonded forces
@@ -1593,17 +1614,16 @@ __device__ __forceinline__ void finish_particle(const StepArgs& a, int64_t i, co
     }
 }
 
+// First row of a step's partial sums: without the tensor the two parities'
+// sums lie side by side, so that a step's are there while the next step runs.
+__device__ __forceinline__ int partial_row(int nacc, int parity) { return nacc < kNacc ? parity * nacc : 0; }
+
 // Flags (one store or atomic per wave) and the deterministic block
 // reduction of the per-particle sums into partials[k][block]; BS threads per
 // block.
 template <int BS = kBlock>
 __device__ __forceinline__ void block_epilogue(const StepArgs& a, const double* acc, bool flag_reb,
-                                              bool flag_bond, bool flag_nf, int nacc, int64_t slot = -1,
-                                              int64_t nslots = 0) {
-    if (slot < 0) {
-        slot = blockIdx.x;
-        nslots = gridDim.x;
-    }
+                                              bool flag_bond, bool flag_nf, int nacc, int64_t slot, int64_t nslots) {
     const Bufs& b = a.b;
     const bool any_reb = __any(flag_reb);
     const bool any_bond = __any(flag_bond);
@@ -1613,8 +1633,9 @@ __device__ __forceinline__ void block_epilogue(const StepArgs& a, const double* 
         // drifting sheared image nearly every wavefront of a step can ask for
         // the rebuild, so a wavefront sets the flag only when it reads it
         // clear; a stale read costs one redundant store, never a lost request.
-        if (any_reb && __hip_atomic_load(&b.ctl->rebuild_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
-            __atomic_store_n(&b.ctl->rebuild_next, 1u, __ATOMIC_RELAXED);
+        uint32_t* const next = &b.ctl->rebuild[a.parity ^ 1];
+        if (any_reb && __hip_atomic_load(next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
+            __atomic_store_n(next, 1u, __ATOMIC_RELAXED);
         if (any_bond) atomicOr(&b.ctl->status, MD_FLAG_BOND_BROKEN);
         if (any_nf) atomicOr(&b.ctl->status, MD_FLAG_NONFINITE);
     }
@@ -1625,12 +1646,116 @@ __device__ __forceinline__ void block_epilogue(const StepArgs& a, const double* 
         if (lane == 0) red[w][q] = s;
     }
     __syncthreads();
-    if (threadIdx.x < kNacc) {
+    if ((int)threadIdx.x < nacc) {
         double s = 0.0;
-        if ((int)threadIdx.x < nacc)
-            for (int ww = 0; ww < BS / 64; ++ww) s += red[ww][threadIdx.x];
-        b.partials[(int64_t)threadIdx.x * nslots + slot] = s;
+        for (int ww = 0; ww < BS / 64; ++ww) s += red[ww][threadIdx.x];
+        b.partials[((int64_t)threadIdx.x + partial_row(nacc, a.parity)) * nslots + slot] = s;
     }
+}
+
+// One block of BS threads: reduce the step's partials[k][block] in a fixed
+// order and record its observables.  MODE_STEP (the end of a call) also
+// advances the step counter; MODE_PREV, the first block of the next step's
+// kernel, finds it advanced.  NACC: the quantities the step kernel summed (the
+// virial tensor only when it was asked for).
+constexpr int kFinal = 1024;
+constexpr int kNaccStep = A_VIR + 1;
+template <int BS, int NACC>
+__device__ __forceinline__ void finalize_body(const Bufs& b, int parity, int nblocks, int mode, const double* spart,
+                                              int spart_rows) {
+    __shared__ double red[BS / 64][NACC];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const double* __restrict__ part = b.partials + (int64_t)partial_row(NACC, parity) * nblocks;
+    double s[NACC];
+#pragma unroll
+    for (int k = 0; k < NACC; ++k) s[k] = 0.0;
+    for (int blk0 = 0; blk0 < nblocks; blk0 += 4 * BS) {
+        double v[4][NACC];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int blk = blk0 + r * BS + threadIdx.x;
+#pragma unroll
+            for (int k = 0; k < NACC; ++k) v[r][k] = blk < nblocks ? part[(int64_t)k * nblocks + blk] : 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int k = 0; k < NACC; ++k) s[k] += v[r][k];
+        if (spart) {
+            // surrogate pair energy (row 0), virial (row 1) and tensor (rows 2..7)
+            for (int r = 0; r < 4; ++r) {
+                const int blk = blk0 + r * BS + threadIdx.x;
+                if (blk >= nblocks) continue;
+                s[A_EPAIR] += spart[blk];
+                if (spart_rows > 1) {
+                    s[A_VIR] += spart[(int64_t)nblocks + blk];
+                    if (NACC == kNacc)
+                        for (int k = 0; k < 6; ++k) s[(A_TXX + k) % NACC] += spart[(int64_t)(2 + k) * nblocks + blk];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NACC; ++k) {
+        const double t = wave_sum(s[k]);
+        if (lane == 0) red[w][k] = t;
+    }
+    __syncthreads();
+    // one lane per quantity sums the wavefront totals (fixed order), so the
+    // serial part below reads finished sums only
+    __shared__ double fin[NACC];
+    if (threadIdx.x < NACC) {
+        double v = 0.0;
+        for (int ww = 0; ww < BS / 64; ++ww) v += red[ww][threadIdx.x];
+        fin[threadIdx.x] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        DevCtl* c = b.ctl;
+        const bool prev = mode == MODE_PREV;
+        const int64_t step = c->step - (prev ? 1 : 0);
+        double rec[kHistRec];
+        rec[H_STEP] = (double)step;
+        rec[H_EPAIR] = fin[A_EPAIR];
+        rec[H_EBOND] = fin[A_EBOND];
+        rec[H_EANGLE] = fin[A_EANGLE];
+        rec[H_EKIN] = fin[A_EKIN];
+        rec[H_VIR] = fin[A_VIR];
+        for (int k = 0; k < 6; ++k) rec[H_T0 + k] = NACC == kNacc ? fin[(A_TXX + k) % NACC] : 0.0;
+        rec[H_NREB] = (double)(prev ? c->prev_rebuilds : c->n_rebuilds);
+        rec[H_STATUS] = (double)(prev ? c->prev_status : c->status);
+        rec[H_NLMAX] = (double)(prev ? c->prev_nl_max : c->nl_max);
+        rec[15] = 0.0;
+        for (int k = 0; k < kHistRec; ++k) b.cur[k] = rec[k];
+        if (prev || mode == MODE_STEP) {
+            double* h = b.hist + (int64_t)(step % MD_HISTORY_CAPACITY) * kHistRec;
+            for (int k = 0; k < kHistRec; ++k) h[k] = rec[k];
+        }
+        if (mode == MODE_STEP) {
+            c->step = step + 1;
+            c->vel_half = 1;
+            c->ran = 0;
+        }
+        if (mode == MODE_OBSERVE || mode == MODE_FORCES) c->rebuild[0] = c->rebuild[1] = 0;
+    }
+}
+
+template <int BS, int NACC>
+__global__ void __launch_bounds__(BS) k_finalize(Bufs b, int parity, int nblocks, int mode, const double* spart,
+                                                 int spart_rows) {
+    finalize_body<BS, NACC>(b, parity, nblocks, mode, spart, spart_rows);
+}
+
+// Block index and grid of a step kernel without the block that writes the
+// previous step's record (StepArgs::fin): true for that block, its work done.
+// It comes first, so that its serial tail lies beside the other blocks' work.
+template <int BS = kBlock>
+__device__ __forceinline__ bool finalize_block(const StepArgs& a, int& blk, int& grid) {
+    blk = (int)blockIdx.x - a.fin;
+    grid = (int)gridDim.x - a.fin;
+    if (blk >= 0) return false;
+    if (a.b.ctl->fin_prev) finalize_body<BS, kNaccStep>(a.b, a.parity ^ 1, grid, MODE_PREV, a.fin_spart, 1);
+    return true;
 }
 
 // ------------------------------------------------------------------ step kernels
@@ -1639,6 +1764,8 @@ __device__ __forceinline__ void block_epilogue(const StepArgs& a, const double* 
 // array, all pair and bonded math in FP64.
 template <bool SINGLE, bool BONDED>
 __global__ void __launch_bounds__(kBlock) k_step64(const StepArgs a) {
+    int blk, grid;
+    if (finalize_block(a, blk, grid)) return;
     const Geom& g = a.g;
     const Bufs& b = a.b;
     const int64_t n = g.n;
@@ -1649,8 +1776,8 @@ __global__ void __launch_bounds__(kBlock) k_step64(const StepArgs a) {
     bool flag_reb = false, flag_bond = false, flag_nf = false;
     const bool tensor = a.tensor != 0;
     const int64_t ntile = (n + kBlock - 1) / kBlock;
-    const int64_t bt = xcd_block(blockIdx.x, gridDim.x);
-    for (int64_t t = bt * ntile / gridDim.x; t < (bt + 1) * ntile / gridDim.x; ++t) {
+    const int64_t bt = xcd_block(blk, grid);
+    for (int64_t t = bt * ntile / grid; t < (bt + 1) * ntile / grid; ++t) {
     const int64_t i = t * kBlock + threadIdx.x;
     if (i < n) {
         const double4 xi = xin[i];
@@ -1697,7 +1824,7 @@ __global__ void __launch_bounds__(kBlock) k_step64(const StepArgs a) {
         finish_particle(a, i, xi, SINGLE ? 0 : ti, F, acc, flag_reb, flag_nf);
     }
     }
-    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : A_VIR + 1);
+    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
 }
 
 // FP32 pair path.  Neighbours are gathered as 16-byte fixed-point records;
@@ -1709,6 +1836,8 @@ __global__ void __launch_bounds__(kBlock) k_step64(const StepArgs a) {
 // the gathers that use them.
 template <bool SINGLE, bool BONDED, bool TENSOR>
 __global__ void __launch_bounds__(kBlock) k_step_q(const StepArgs a) {
+    int blk, grid;
+    if (finalize_block(a, blk, grid)) return;
     const Geom& g = a.g;
     const Bufs& b = a.b;
     const int64_t n = g.n;
@@ -1719,8 +1848,8 @@ __global__ void __launch_bounds__(kBlock) k_step_q(const StepArgs a) {
     for (int k = 0; k < kNacc; ++k) acc[k] = 0.0;
     bool flag_reb = false, flag_bond = false, flag_nf = false;
     const int64_t ntile = (n + kBlock - 1) / kBlock;
-    const int64_t bt = xcd_block(blockIdx.x, gridDim.x);
-    for (int64_t t = bt * ntile / gridDim.x; t < (bt + 1) * ntile / gridDim.x; ++t) {
+    const int64_t bt = xcd_block(blk, grid);
+    for (int64_t t = bt * ntile / grid; t < (bt + 1) * ntile / grid; ++t) {
     const int64_t i = t * kBlock + threadIdx.x;
     if (i < n) {
         const double4 xi = x64[i];
@@ -1823,7 +1952,7 @@ __global__ void __launch_bounds__(kBlock) k_step_q(const StepArgs a) {
         finish_particle(a, i, xi, SINGLE ? 0 : ti, F, acc, flag_reb, flag_nf);
     }
     }
-    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : A_VIR + 1);
+    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : kNaccStep, blk, grid);
 }
 
 
@@ -1949,18 +2078,20 @@ __device__ __forceinline__ void fast_particle(const StepArgs& a, int64_t i, doub
 // picks); one block per BS-particle tile, blocks in XCD-contiguous order.
 template <bool BONDED, bool TENSOR, int BS>
 __device__ __forceinline__ void step_fast_body(const StepArgs& a) {
+    int blk, grid;
+    if (finalize_block<BS>(a, blk, grid)) return;
     const int64_t n = a.g.n;
     double acc[kNacc];
 #pragma unroll
     for (int k = 0; k < kNacc; ++k) acc[k] = 0.0;
     bool flag_reb = false, flag_bond = false, flag_nf = false;
     const int64_t ntile = (n + BS - 1) / BS;
-    const int64_t bt = xcd_block(blockIdx.x, gridDim.x);
-    for (int64_t t = bt * ntile / gridDim.x; t < (bt + 1) * ntile / gridDim.x; ++t) {
+    const int64_t bt = xcd_block(blk, grid);
+    for (int64_t t = bt * ntile / grid; t < (bt + 1) * ntile / grid; ++t) {
         const int64_t i = t * BS + threadIdx.x;
         if (i < n) fast_particle<BONDED, TENSOR>(a, i, acc, flag_reb, flag_bond, flag_nf);
     }
-    block_epilogue<BS>(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : A_VIR + 1);
+    block_epilogue<BS>(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : kNaccStep, blk, grid);
 }
 
 // The LJ form: 139-142 VGPRs, 3 wavefronts per SIMD, at every block size.
@@ -2030,6 +2161,8 @@ __device__ __forceinline__ float dpd_theta(uint64_t seed, uint64_t step, uint32_
 template <bool BONDED, bool SINGLE, bool LDSTAB>
 __global__ void __launch_bounds__(kBlock) k_step_gen(const StepArgs a) {
     extern __shared__ float2 stab[];
+    int blk, grid;
+    if (finalize_block(a, blk, grid)) return;
     const Geom& g = a.g;
     const Bufs& b = a.b;
     const int64_t n = g.n;
@@ -2062,7 +2195,7 @@ __global__ void __launch_bounds__(kBlock) k_step_gen(const StepArgs a) {
         les.drift = fabs(g.le_rate_Ly * ((double)(step + 1 - b.ctl->build_step) * g.le_dt));
     }
     const bool dpd = a.dy.dpd && a.mode == MODE_STEP;
-    const int64_t i = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    const int64_t i = (int64_t)xcd_block(blk, grid) * kBlock + threadIdx.x;
     if (i < n) {
         const double4 xi = x64[i];
         const int4 qi = quantize4(g, xi.x, xi.y, xi.z, xi.w);
@@ -2196,7 +2329,7 @@ __global__ void __launch_bounds__(kBlock) k_step_gen(const StepArgs a) {
         const double F[3] = {(double)fx, (double)fy, (double)fz};
         finish_particle(a, i, xi, ti, F, acc, flag_reb, flag_nf, g.le ? &les : nullptr);
     }
-    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : A_VIR + 1);
+    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
 }
 
 // Step of the surrogate mode, one 256-particle tile per block: the
@@ -2215,6 +2348,8 @@ typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 
 template <bool BONDED, bool TENSOR, bool A16>
 __global__ void __launch_bounds__(kBlock) k_sur_step(const StepArgs a, const SurBufs s, const SurConst c) {
+    int blk, grid;
+    if (finalize_block(a, blk, grid)) return;
     constexpr int AW = A16 ? 16 : 32;       // 32-bit words per a row
     const Geom& g = a.g;
     const Bufs& b = a.b;
@@ -2223,7 +2358,7 @@ __global__ void __launch_bounds__(kBlock) k_sur_step(const StepArgs a, const Sur
 #pragma unroll
     for (int k = 0; k < kNacc; ++k) acc[k] = 0.0;
     bool flag_reb = false, flag_bond = false, flag_nf = false;
-    const int64_t i = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    const int64_t i = (int64_t)xcd_block(blk, grid) * kBlock + threadIdx.x;
     if (i < n) {
         const int4* __restrict__ xq = b.xq[a.parity];
         const double4 xi = b.x[a.parity][i];
@@ -2342,98 +2477,7 @@ __global__ void __launch_bounds__(kBlock) k_sur_step(const StepArgs a, const Sur
         const double F[3] = {(double)fx, (double)fy, (double)fz};
         finish_particle(a, i, xi, (int)xi.w, F, acc, flag_reb, flag_nf);
     }
-    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : A_VIR + 1);
-}
-
-// One block: reduce partials[k][block] in a fixed order, record the step's
-// observables, and (MODE_STEP) advance the step counter and move the
-// rebuild request to the next step.
-constexpr int kFinal = 1024;
-// nacc: the number of quantities the step kernel accumulated (the virial
-// tensor only when it was asked for); the others are zero and not read.
-__device__ __forceinline__ void finalize_body(const Bufs& b, int nblocks, int mode, const double* spart, int nacc,
-                                              int spart_rows = 8) {
-    __shared__ double red[kFinal / 64][kNacc];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    double s[kNacc];
-#pragma unroll
-    for (int k = 0; k < kNacc; ++k) s[k] = 0.0;
-    for (int blk0 = 0; blk0 < nblocks; blk0 += 4 * kFinal) {
-        double v[4][kNacc];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int blk = blk0 + r * kFinal + threadIdx.x;
-#pragma unroll
-            for (int k = 0; k < kNacc; ++k)
-                v[r][k] = (k < nacc && blk < nblocks) ? b.partials[(int64_t)k * nblocks + blk] : 0.0;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int k = 0; k < kNacc; ++k) s[k] += v[r][k];
-        if (spart) {
-            // surrogate pair energy (row 0), virial (row 1) and tensor (rows 2..7)
-            for (int r = 0; r < 4; ++r) {
-                const int blk = blk0 + r * kFinal + threadIdx.x;
-                if (blk >= nblocks) continue;
-                s[A_EPAIR] += spart[blk];
-                if (spart_rows > 1) {
-                    s[A_VIR] += spart[(int64_t)nblocks + blk];
-                    if (nacc == kNacc)
-                        for (int k = 0; k < 6; ++k) s[A_TXX + k] += spart[(int64_t)(2 + k) * nblocks + blk];
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < kNacc; ++k) {
-        const double t = k < nacc ? wave_sum(s[k]) : 0.0;
-        if (lane == 0) red[w][k] = t;
-    }
-    __syncthreads();
-    // one lane per quantity sums the wavefront totals (fixed order), so the
-    // serial part below reads finished sums only
-    __shared__ double fin[kNacc];
-    if (threadIdx.x < kNacc) {
-        double v = 0.0;
-        for (int ww = 0; ww < kFinal / 64; ++ww) v += red[ww][threadIdx.x];
-        fin[threadIdx.x] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double tot[kNacc];
-        for (int k = 0; k < kNacc; ++k) tot[k] = fin[k];
-        DevCtl* c = b.ctl;
-        const int64_t step = c->step;
-        double rec[kHistRec];
-        rec[H_STEP] = (double)step;
-        rec[H_EPAIR] = tot[A_EPAIR];
-        rec[H_EBOND] = tot[A_EBOND];
-        rec[H_EANGLE] = tot[A_EANGLE];
-        rec[H_EKIN] = tot[A_EKIN];
-        rec[H_VIR] = tot[A_VIR];
-        for (int k = 0; k < 6; ++k) rec[H_T0 + k] = tot[A_TXX + k];
-        rec[H_NREB] = (double)c->n_rebuilds;
-        rec[H_STATUS] = (double)c->status;
-        rec[H_NLMAX] = (double)c->nl_max;
-        rec[15] = 0.0;
-        for (int k = 0; k < kHistRec; ++k) b.cur[k] = rec[k];
-        if (mode == MODE_STEP) {
-            double* h = b.hist + (int64_t)(step % MD_HISTORY_CAPACITY) * kHistRec;
-            for (int k = 0; k < kHistRec; ++k) h[k] = rec[k];
-            c->step = step + 1;
-            c->vel_half = 1;
-            c->rebuild = c->rebuild_next;
-            c->rebuild_next = 0;
-        } else {
-            c->rebuild = 0;
-        }
-    }
-}
-
-__global__ void __launch_bounds__(kFinal) k_finalize(Bufs b, int nblocks, int mode, const double* spart, int nacc,
-                                                     int spart_rows) {
-    finalize_body(b, nblocks, mode, spart, nacc, spart_rows);
+    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : kNaccStep, blk, grid);
 }
 
 // ------------------------------------------------------------------ batches
@@ -2448,8 +2492,9 @@ struct TileRef {
     int64_t i;      // particle inside the system
 };
 
-__device__ __forceinline__ TileRef tile_ref(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_sys) {
-    const int64_t t = xcd_block(blockIdx.x, gridDim.x);
+__device__ __forceinline__ TileRef tile_ref(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_sys,
+                                            int blk, int grid) {
+    const int64_t t = xcd_block(blk, grid);
     const SysEntry* e = tab + tile_sys[t];
     const int64_t lt = t - e->tile0;
     return TileRef{e, lt, lt * kBlock + threadIdx.x};
@@ -2468,49 +2513,53 @@ __device__ __forceinline__ TileRef tile_ref_spread(const SysEntry* __restrict__ 
     return TileRef{e, lt, lt * kBlock + threadIdx.x};
 }
 
-__global__ void k_batch_any(BatchCells bc) {
+// Starts every member's step (advance) and asks whether any rebuilds.
+__global__ void k_batch_any(BatchCells bc, int parity, int advance) {
     __shared__ int any;
     if (threadIdx.x == 0) any = 0;
     __syncthreads();
-    for (int s = threadIdx.x; s < bc.nsys; s += blockDim.x)
-        if (rebuild_requested(bc.tab[s].a.b)) any = 1;
+    for (int s = threadIdx.x; s < bc.nsys; s += blockDim.x) {
+        const Bufs& b = bc.tab[s].a.b;
+        if (advance) advance_step(b, parity);
+        if (rebuild_requested(b, parity)) any = 1;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) bc.gb.ctl->rebuild = (uint32_t)any;
+    if (threadIdx.x == 0) bc.gb.ctl->rebuild[0] = (uint32_t)any;
 }
 
 __global__ void __launch_bounds__(kBlock) k_batch_bin(const SysEntry* __restrict__ tab,
                                                       const int32_t* __restrict__ tile_sys, int parity) {
     const TileRef r = tile_ref_spread(tab, tile_sys);
     const Bufs& b = r.e->a.b;
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, parity)) return;
     const Geom& g = r.e->a.g;
     bin_one(g, b, r.i, r.i < g.n, parity);
 }
 
 // prefix of the concatenated counts at each system's first cell
 __global__ void k_batch_bases(BatchCells bc) {
-    if (!rebuild_requested(bc.gb)) return;
+    if (!rebuild_requested(bc.gb, 0)) return;
     for (int s = threadIdx.x; s < bc.nsys; s += blockDim.x) bc.base[s] = bc.gb.cstart[bc.c_off[s]];
 }
 
 // cell starts of rebuilding systems become offsets inside the system
-__global__ void __launch_bounds__(kBlock) k_batch_localize(BatchCells bc) {
-    if (!rebuild_requested(bc.gb)) return;
+__global__ void __launch_bounds__(kBlock) k_batch_localize(BatchCells bc, int parity) {
+    if (!rebuild_requested(bc.gb, 0)) return;
     for (int64_t c = gtid(); c < bc.gg.ncell; c += gstride()) {
         int lo = 0, hi = bc.nsys;   // system with c_off[s] <= c < c_off[s + 1]
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
             if (bc.c_off[mid] <= c) lo = mid; else hi = mid;
         }
-        if (rebuild_requested(bc.tab[lo].a.b)) bc.gb.cstart[c] -= bc.base[lo];
+        if (rebuild_requested(bc.tab[lo].a.b, parity)) bc.gb.cstart[c] -= bc.base[lo];
     }
 }
 
 __global__ void __launch_bounds__(kBlock) k_batch_scatter(const SysEntry* __restrict__ tab,
-                                                          const int32_t* __restrict__ tile_sys) {
+                                                          const int32_t* __restrict__ tile_sys, int parity) {
     const TileRef r = tile_ref_spread(tab, tile_sys);
     const Bufs& b = r.e->a.b;
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, parity)) return;
     scatter_one(b, r.i, r.i < r.e->a.g.n);
 }
 
@@ -2518,7 +2567,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_permute(const SysEntry* __rest
                                                           const int32_t* __restrict__ tile_sys, int parity) {
     const TileRef r = tile_ref_spread(tab, tile_sys);
     const Bufs& b = r.e->a.b;
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, parity)) return;
     const Geom& g = r.e->a.g;
     if (r.i < g.n) permute_one(g, b, r.i, parity);
 }
@@ -2527,7 +2576,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_commit(const SysEntry* __restr
                                                          const int32_t* __restrict__ tile_sys, int parity) {
     const TileRef r = tile_ref_spread(tab, tile_sys);
     const Bufs& b = r.e->a.b;
-    if (!rebuild_requested(b)) return;
+    if (!rebuild_requested(b, parity)) return;
     const Geom& g = r.e->a.g;
     if (r.i < g.n) commit_one(g, b, r.i, parity, r.e->bonded);
 }
@@ -2538,7 +2587,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_nl(const SysEntry* __restrict_
     const TileRef r = tile_ref_spread(tab, tile_sys);
     const Bufs& b = r.e->a.b;
     const Geom& g = r.e->a.g;
-    if (g.nl_mat || !rebuild_requested(b)) return;
+    if (g.nl_mat || !rebuild_requested(b, parity)) return;
     int local_max = 0;
     bool overflow = false;
     if (r.i < g.n) nl_one(g, b, r.i, parity, r.e->bonded, local_max, overflow);
@@ -2553,7 +2602,7 @@ __global__ void __launch_bounds__(kTile) k_batch_nl_mtile(const SysEntry* __rest
     const SysEntry* e = tab + tile_sys[blockIdx.x / (kBlock / kTile)];
     const Bufs& b = e->a.b;
     const Geom& g = e->a.g;
-    if (!g.nl_mat || !rebuild_requested(b)) return;
+    if (!g.nl_mat || !rebuild_requested(b, parity)) return;
     const int64_t t = (int64_t)blockIdx.x - e->tile0 * (kBlock / kTile);
     if (t * kTile >= g.n) return;
     int local_max = 0;
@@ -2570,8 +2619,14 @@ __global__ void __launch_bounds__(kTile) k_batch_nl_mtile(const SysEntry* __rest
 // melts): 637 -> 615 us per step for the 256-replica batch.
 template <bool TENSOR>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
-k_batch_step(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_sys) {
-    const TileRef r = tile_ref(tab, tile_sys);
+k_batch_step(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_sys, int nfin) {
+    if ((int)blockIdx.x < nfin) {   // a member's previous step's record
+        const SysEntry& e = tab[blockIdx.x];
+        if (e.a.b.ctl->fin_prev)
+            finalize_body<kBlock, kNaccStep>(e.a.b, e.a.parity ^ 1, e.ntiles, MODE_PREV, nullptr, 1);
+        return;
+    }
+    const TileRef r = tile_ref(tab, tile_sys, (int)blockIdx.x - nfin, (int)gridDim.x - nfin);
     const StepArgs& a = r.e->a;
     double acc[kNacc];
 #pragma unroll
@@ -2581,12 +2636,13 @@ k_batch_step(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_
         if (r.e->bonded) fast_particle<true, TENSOR>(a, r.i, acc, flag_reb, flag_bond, flag_nf);
         else fast_particle<false, TENSOR>(a, r.i, acc, flag_reb, flag_bond, flag_nf);
     }
-    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : A_VIR + 1, r.lt, r.e->ntiles);
+    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : kNaccStep, r.lt, r.e->ntiles);
 }
 
-__global__ void __launch_bounds__(kFinal) k_batch_finalize(const SysEntry* __restrict__ tab, int mode) {
+template <int BS, int NACC>
+__global__ void __launch_bounds__(BS) k_batch_finalize(const SysEntry* __restrict__ tab, int mode) {
     const SysEntry& e = tab[blockIdx.x];
-    finalize_body(e.a.b, e.ntiles, mode, nullptr, kNacc);
+    finalize_body<BS, NACC>(e.a.b, e.a.parity, e.ntiles, mode, nullptr, 1);
 }
 
 __global__ void k_batch_gather_obs(const SysEntry* __restrict__ tab, int nsys, double* out) {
@@ -2660,15 +2716,15 @@ hipError_t launch_clear_rebuild(const Bufs& b, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_rebuild(const Geom& g, const Bufs& b, int parity, int bonded, hipStream_t s,
+hipError_t launch_rebuild(const Geom& g, const Bufs& b, int parity, int bonded, int advance, hipStream_t s,
                           hipEvent_t ev_sorted) {
     // the sort passes stride over the particles with at most 2048 blocks:
     // against 512 (2M-bead melt, binning and sort per step) 62.0 -> 56.4 us,
     // and one block per 256 particles 59.2 us
     const int gs = grid_for(g.n, 2048);
-    hipLaunchKernelGGL(k_bin, dim3(gs), dim3(kBlock), 0, s, g, b, parity);
-    hipLaunchKernelGGL(k_scan_chunks, dim3(kScanBlocks), dim3(kBlock), 0, s, g, b);
-    hipLaunchKernelGGL(k_scatter, dim3(gs), dim3(kBlock), 0, s, g, b);
+    hipLaunchKernelGGL(k_bin, dim3(gs), dim3(kBlock), 0, s, g, b, parity, advance);
+    hipLaunchKernelGGL(k_scan_chunks, dim3(kScanBlocks), dim3(kBlock), 0, s, g, b, parity);
+    hipLaunchKernelGGL(k_scatter, dim3(gs), dim3(kBlock), 0, s, g, b, parity);
     hipLaunchKernelGGL(k_rank_permute, dim3(gs), dim3(kBlock), 0, s, g, b, parity);
     hipLaunchKernelGGL(k_commit, dim3(gs), dim3(kBlock), 0, s, g, b, parity, bonded);
     if (ev_sorted) (void)hipEventRecord(ev_sorted, s);
@@ -2693,7 +2749,7 @@ int step_launch_grid(const StepArgs& a, int fp64, int block) {
 
 template <bool BONDED, bool TENSOR>
 static void launch_fast(const StepArgs& a, int block, hipStream_t s) {
-    const dim3 grid((unsigned)step_launch_grid(a, 0, block)), blk((unsigned)block);
+    const dim3 grid((unsigned)(step_launch_grid(a, 0, block) + a.fin)), blk((unsigned)block);
 #define MD_LF(BS)                                                                                  \
     do {                                                                                           \
         if (BONDED) hipLaunchKernelGGL((k_step_fast_bonded<TENSOR, BS>), grid, blk, 0, s, a);     \
@@ -2717,7 +2773,7 @@ __global__ void __launch_bounds__(kBlock) k_snapshot_v(const Bufs b, int64_t n) 
 }
 
 hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded, int block, hipStream_t s) {
-    dim3 grid((unsigned)step_grid(a.g.n)), blk(kBlock);
+    dim3 grid((unsigned)(step_grid(a.g.n) + a.fin)), blk(kBlock);
     if (a.dy.gen && a.dy.dpd && a.mode == MODE_STEP)
         hipLaunchKernelGGL(k_snapshot_v, dim3(grid_for(a.g.n)), dim3(kBlock), 0, s, a.b, a.g.n);
     if (a.dy.gen) {
@@ -2764,16 +2820,22 @@ hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded,
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(const Bufs& b, int nblocks, int mode, const double* spart, int tensor, hipStream_t s,
-                           int spart_rows) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinal), 0, s, b, nblocks, mode, spart, tensor ? kNacc : A_VIR + 1,
-                       spart_rows);
+hipError_t launch_finalize(const Bufs& b, int parity, int nblocks, int block, int mode, const double* spart,
+                           int tensor, hipStream_t s, int spart_rows) {
+#define MD_FIN(BS, NA) \
+    hipLaunchKernelGGL((k_finalize<BS, NA>), dim3(1), dim3(BS), 0, s, b, parity, nblocks, mode, spart, spart_rows)
+    if (tensor) MD_FIN(kFinal, kNacc);
+    else if (block == 64) MD_FIN(64, kNaccStep);
+    else if (block == 128) MD_FIN(128, kNaccStep);
+    else if (block == 512) MD_FIN(512, kNaccStep);
+    else MD_FIN(kBlock, kNaccStep);
+#undef MD_FIN
     return hipGetLastError();
 }
 
 hipError_t launch_sur_step(const StepArgs& a, const SurBufs& sb, const SurConst& c, int bonded, int a_bf16,
                            hipStream_t s) {
-    dim3 grid((unsigned)step_grid(a.g.n)), blk(kBlock);
+    dim3 grid((unsigned)(step_grid(a.g.n) + a.fin)), blk(kBlock);
     const bool t = a.tensor != 0;
 #define MD_LS(BO, T, A) hipLaunchKernelGGL((k_sur_step<BO, T, A>), grid, blk, 0, s, a, sb, c)
     if (a_bf16) {
@@ -2792,16 +2854,16 @@ hipError_t launch_sur_step(const StepArgs& a, const SurBufs& sb, const SurConst&
 namespace md {
 
 hipError_t launch_batch_rebuild(const BatchCells& bc, const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles,
-                                int parity, hipStream_t s, hipEvent_t ev_sorted) {
+                                int parity, int advance, hipStream_t s, hipEvent_t ev_sorted) {
     const dim3 tg((unsigned)ntiles), blk(kBlock);
-    hipLaunchKernelGGL(k_batch_any, dim3(1), dim3(256), 0, s, bc);
+    hipLaunchKernelGGL(k_batch_any, dim3(1), dim3(256), 0, s, bc, parity, advance);
     hipLaunchKernelGGL(k_batch_bin, tg, blk, 0, s, tab, tile_sys, parity);
     hipLaunchKernelGGL(k_scan_reduce, dim3(kScanBlocks), dim3(kBlock), 0, s, bc.gg, bc.gb);
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanBlocks), 0, s, bc.gb);
     hipLaunchKernelGGL(k_scan_apply, dim3(kScanBlocks), dim3(kBlock), 0, s, bc.gg, bc.gb);
     hipLaunchKernelGGL(k_batch_bases, dim3(1), dim3(256), 0, s, bc);
-    hipLaunchKernelGGL(k_batch_localize, dim3(grid_for(bc.gg.ncell, 4096)), blk, 0, s, bc);
-    hipLaunchKernelGGL(k_batch_scatter, tg, blk, 0, s, tab, tile_sys);
+    hipLaunchKernelGGL(k_batch_localize, dim3(grid_for(bc.gg.ncell, 4096)), blk, 0, s, bc, parity);
+    hipLaunchKernelGGL(k_batch_scatter, tg, blk, 0, s, tab, tile_sys, parity);
     hipLaunchKernelGGL(k_batch_permute, tg, blk, 0, s, tab, tile_sys, parity);
     hipLaunchKernelGGL(k_batch_commit, tg, blk, 0, s, tab, tile_sys, parity);
     if (ev_sorted) (void)hipEventRecord(ev_sorted, s);
@@ -2812,19 +2874,20 @@ hipError_t launch_batch_rebuild(const BatchCells& bc, const SysEntry* tab, const
     return hipGetLastError();
 }
 
-hipError_t launch_batch_step(const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles, int parity, int mode,
+hipError_t launch_batch_step(const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles, int nsys, int fin,
                              int tensor, hipStream_t s) {
-    (void)parity;
-    (void)mode;
-    if (tensor)
-        hipLaunchKernelGGL(k_batch_step<true>, dim3((unsigned)ntiles), dim3(kBlock), 0, s, tab, tile_sys);
-    else
-        hipLaunchKernelGGL(k_batch_step<false>, dim3((unsigned)ntiles), dim3(kBlock), 0, s, tab, tile_sys);
+    const int nfin = fin ? nsys : 0;
+    const dim3 grid((unsigned)(ntiles + nfin));
+    if (tensor) hipLaunchKernelGGL(k_batch_step<true>, grid, dim3(kBlock), 0, s, tab, tile_sys, nfin);
+    else hipLaunchKernelGGL(k_batch_step<false>, grid, dim3(kBlock), 0, s, tab, tile_sys, nfin);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_finalize(const SysEntry* tab, int nsys, int mode, hipStream_t s) {
-    hipLaunchKernelGGL(k_batch_finalize, dim3(nsys), dim3(kFinal), 0, s, tab, mode);
+    if (mode == MODE_STEP)
+        hipLaunchKernelGGL((k_batch_finalize<kBlock, kNaccStep>), dim3(nsys), dim3(kBlock), 0, s, tab, mode);
+    else
+        hipLaunchKernelGGL((k_batch_finalize<kFinal, kNacc>), dim3(nsys), dim3(kFinal), 0, s, tab, mode);
     return hipGetLastError();
 }
 

@@ -965,9 +965,10 @@ __device__ __forceinline__ void desc_row(const Geom& g, const Bufs& b, const Sur
 // NET = false: the FP32 rows go to s.G.  NET = true: each wavefront runs the
 // BF16 network on its 64 particles straight from registers and LDS, writes
 // the BF16 input gradients a_i to s.ab and the block's energy sum to
-// s.part row 0; the descriptors never reach HBM.
+// epart; the descriptors never reach HBM.
 template <bool NET>
-__global__ void __launch_bounds__(kBlock) k_sur_desc2(Geom g, Bufs b, SurBufs s, SurConst c, int parity) {
+__global__ void __launch_bounds__(kBlock) k_sur_desc2(Geom g, Bufs b, SurBufs s, SurConst c, int parity,
+                                                     double* __restrict__ epart) {
     const int64_t n = g.n;
     const int64_t tile = xcd_block(blockIdx.x, gridDim.x);
     const int64_t i = tile * kBlock + threadIdx.x;
@@ -1016,7 +1017,7 @@ __global__ void __launch_bounds__(kBlock) k_sur_desc2(Geom g, Bufs b, SurBufs s,
                 *reinterpret_cast<const uint4*>(xw + r * kXS + 8 * part);
     }
     double esum = ok ? (double)es[w][lane] : 0.0;
-    block_store<1>(&esum, s.part);
+    block_store<1>(&esum, epart);
 }
 
 // The BF16 network on given descriptor rows G [P][32] (raw; the handle's
@@ -1094,12 +1095,12 @@ hipError_t launch_sur_force(const Geom& g, const Bufs& b, const SurBufs& s, cons
 }
 
 hipError_t launch_sur_desc2(const Geom& g, const Bufs& b, const SurBufs& s, const SurConst& c, int parity, int net,
-                            hipStream_t st) {
+                            hipStream_t st, double* epart) {
     const dim3 grid((unsigned)((g.n + kBlock - 1) / kBlock)), blk(kBlock);
     if (net)
-        hipLaunchKernelGGL(k_sur_desc2<true>, grid, blk, 0, st, g, b, s, c, parity);
+        hipLaunchKernelGGL(k_sur_desc2<true>, grid, blk, 0, st, g, b, s, c, parity, epart);
     else
-        hipLaunchKernelGGL(k_sur_desc2<false>, grid, blk, 0, st, g, b, s, c, parity);
+        hipLaunchKernelGGL(k_sur_desc2<false>, grid, blk, 0, st, g, b, s, c, parity, epart);
     return hipGetLastError();
 }
 
