@@ -128,8 +128,9 @@ typedef struct md_config {
                                   of 8 (rows are streamed in batches of 8 slots);
                                   0 = from density */
     int32_t block_size;        /* particles (threads) per block of the FP32 fast force
-                                  kernels: 64, 128, 256 or 512; 0 = 256.  The other force
-                                  kernels and batches keep 256.  Changes cost only: every
+                                  kernels: 64, 128, 256 or 512; 0 = 64 up to 65,536
+                                  particles, else 256.  The other force kernels take the
+                                  latter, batches 256.  Changes cost only: every
                                   particle's force is computed alone, and only the order
                                   of the FP64 energy/virial block sums follows it */
     int32_t flags;             /* MD_CFG_* */

@@ -287,6 +287,14 @@ static md_status plan_geom(const md_config* c, Geom* g, std::string* why) {
     // are minimum images only with 2 kc + 2 cells per side; smaller boxes build
     // one particle per lane.
     g->nl_mat = (density * rv * rv * rv >= 5.0 || (c->flags & MD_CFG_NL_TILES)) && mat_build_fits(c, g) ? 1 : 0;
+    // One wavefront per particle for small systems, which leave the GPU idle
+    // one particle per lane.  Measured per md_build_neighbors call (LJ, tiles
+    // against this): 2,048 particles 116 / 34 us, 16,384 78 / 53, 33,333 75 /
+    // 73; melts, per particle against this: 1,000 59 / 22, 16,000 69 / 54,
+    // 64,000 69 / 95.  The work limit keeps very dense systems on tiles.
+    const double cand = density * g->h[0] * g->h[1] * g->h[2] * (2 * g->kc + 1) * (2 * g->kc + 1) * (2 * g->kc + 1);
+    g->nl_wave = c->shear_rate == 0.0 && !(c->flags & (MD_CFG_NL_PER_PARTICLE | MD_CFG_NL_TILES)) &&
+                 c->n_particles <= 20000 && (double)c->n_particles * cand <= 1.2e7 ? 1 : 0;
     // the unbonded fast step kernel gathers 12-byte records (fewer L1 lines per
     // gather: 4% faster on the LJ fluid); the bonded one keeps the 16-byte
     // records, for which the extra stores cost more than the gathers save
@@ -551,7 +559,14 @@ static void fill_sur_const(SurConst* c) {
     c->ratio = (float)exp2(-2.0 * (1.4426950408889634 / (2.0 * w2)) * dmu * dmu);
 }
 
-static int block_of(md_handle h) { return h->cfg.block_size ? h->cfg.block_size : kBlock; }
+// Threads per block of the plain force kernels.  Small systems take one
+// wavefront per block, so that all CUs share the gathers: measured per step,
+// 256 against 64 threads: 33,333 LJ particles 18.3 / 17.2 us, 10,000 capped
+// ones 15.8 / 14.8; at 131,000 (FP64) the two are equal.
+static int block_of(md_handle h) {
+    const int automatic = h->g.n <= kSmallBlocks ? 64 : kBlock;
+    return h->use_fast && !h->fp64 && h->cfg.block_size ? h->cfg.block_size : automatic;
+}
 
 // Force stage: the plain fused kernel, or the surrogate's network stage
 // followed by its fused pair-force + bonded + integration kernel.  BF16
@@ -589,9 +604,8 @@ static hipError_t launch_force_stage(md_handle h, int mode, int tensor, double* 
 static hipError_t launch_stage_finalize(md_handle h, int parity, int mode, const double* spart, int tensor) {
     int nb = h->step_grid, block = kBlock;
     if (h->pair_mode == MD_PAIR_PLAIN) {
-        const StepArgs a = make_args(h, mode, tensor, nullptr);
-        nb = step_launch_grid(a, h->fp64, block_of(h));
-        if (!a.dy.gen && !h->fp64 && a.use_fast) block = block_of(h);
+        block = block_of(h);
+        nb = step_launch_grid(h->g.n, block);
     }
     return launch_finalize(h->b, parity, nb, block, mode, spart, tensor, h->stream, 1);
 }

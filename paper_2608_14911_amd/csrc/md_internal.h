@@ -105,6 +105,7 @@ struct Geom {
     int32_t nl_tile;        // the plan's list build (md_plan.nl_build)
     int32_t nl_mat;         // the list is built on the matrix cores, one wavefront per
                             // 64-particle tile; 0: one particle per lane
+    int32_t nl_wave;        // a small system's list: one wavefront per particle
     int32_t x3_on;          // keep the 12-byte position records (systems without bonds,
                             // whose fast step kernel gathers them)
     // Lees-Edwards shear (flow x, gradient y): offset delta(step) =
@@ -349,9 +350,10 @@ hipError_t launch_clear_rebuild(const Bufs& b, hipStream_t s);
 hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded, int block,
                        hipStream_t s);
 int step_grid(int64_t n);
-// blocks of the plain force kernel that launch_step runs with `block`
-// threads per block (the FP32 fast kernels take 64..512; the others 256)
-int step_launch_grid(const StepArgs& a, int fp64, int block);
+// blocks of the plain force kernel that launch_step runs with `block` threads
+// per block (the FP32 fast kernels take 64, 128, 256 or 512, the others 64 or 256)
+int step_launch_grid(int64_t n, int block);
+constexpr int64_t kSmallBlocks = 65536;     // systems up to this take 64-thread blocks by default
 // spart: surrogate partials (row 0 energy; with spart_rows 8 also virial and
 // tensor rows), or nullptr
 // block: threads of the step kernel's blocks; parity: of the step finalized

@@ -546,6 +546,61 @@ __global__ void __launch_bounds__(kBlock) k_commit(Geom g, Bufs b, int parity, i
     for (int64_t s = gtid(); s < g.n; s += gstride()) commit_one(g, b, s, parity, bonded);
 }
 
+// The whole sort of a small system by one block: counts and cursors in LDS,
+// the passes separated by block barriers.  A step that rebuilds nothing then
+// launches one kernel for the sort instead of five (each launch that returns
+// costs 1.5-2.9 us), and one that does pays no launch gaps.
+constexpr int kSmallSort = 4096;    // particles
+constexpr int kSmallCells = 8192;   // cells (32 KB of LDS)
+constexpr int kSmallBlock = 1024;
+__global__ void __launch_bounds__(kSmallBlock) k_sort_small(Geom g, Bufs b, int parity, int bonded, int advance) {
+    __shared__ int cnt[kSmallCells];
+    __shared__ int wsum[kSmallBlock / 64];
+    if (advance && threadIdx.x == 0) advance_step(b, parity);
+    if (!rebuild_requested(b, parity)) return;
+    const int n = (int)g.n, ncell = (int)g.ncell, tid = threadIdx.x;
+    for (int c = tid; c < ncell; c += kSmallBlock) cnt[c] = 0;
+    __syncthreads();
+    for (int i = tid; i < n; i += kSmallBlock) {
+        const uint32_t c = cell_of(g, b.x[parity][i]);
+        b.cellid[i] = c;
+        atomicAdd(&cnt[c], 1);
+    }
+    __syncthreads();
+    // exclusive scan, a run of consecutive cells per thread
+    const int per = (ncell + kSmallBlock - 1) / kSmallBlock;
+    const int c0 = min(tid * per, ncell), c1 = min(c0 + per, ncell);
+    int sum = 0;
+    for (int c = c0; c < c1; ++c) sum += cnt[c];
+    int x = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if ((tid & 63) >= o) x += y;
+    }
+    if ((tid & 63) == 63) wsum[tid >> 6] = x;
+    __syncthreads();
+    int e = x - sum;
+    for (int w = 0; w < (tid >> 6); ++w) e += wsum[w];
+    for (int c = c0; c < c1; ++c) {
+        const int k = cnt[c];
+        cnt[c] = e;
+        b.cstart[c] = e;
+        e += k;
+    }
+    if (tid == 0) b.cstart[ncell] = n;
+    __syncthreads();
+    for (int i = tid; i < n; i += kSmallBlock) {
+        const int slot = atomicAdd(&cnt[b.cellid[i]], 1);
+        b.tmp[slot] = i;
+        b.tsc[slot] = b.tag[i];
+    }
+    __syncthreads();
+    for (int s = tid; s < n; s += kSmallBlock) permute_one(g, b, s, parity);
+    __syncthreads();
+    for (int s = tid; s < n; s += kSmallBlock) commit_one(g, b, s, parity, bonded);
+}
+
 // ------------------------------------------------------------------ rebuild: Verlet list
 
 // r_ij^2 in FP64 with the operation order of the plain definition
@@ -769,6 +824,97 @@ __global__ void __launch_bounds__(kBlock) k_nl_build(Geom g, Bufs b, int parity,
     bool overflow = false;
     for (int64_t i = gtid_xcd(); i < g.n; i += gstride()) nl_one(g, b, i, parity, bonded, local_max, overflow);
     nl_epilogue(b, local_max, overflow);
+}
+
+// The same lists, one wavefront per particle, for systems whose particles
+// leave the GPU idle one per lane: the particle's stencil ranges are bounded by
+// one lane each, their candidates tested 64 at a time and the hits compacted by
+// ballot, so a row takes a few memory round trips instead of one per stencil
+// row and candidate group.  Row order and decisions as nl_one.
+__global__ void __launch_bounds__(kBlock) k_nl_wave(Geom g, Bufs b, int parity, int bonded) {
+    if (!rebuild_requested(b, parity)) return;
+    const int lane = threadIdx.x & 63;
+    const int64_t n = g.n;
+    const int i = (int)((int64_t)blockIdx.x * (kBlock / 64)) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+    if (i >= n) return;
+    const double4* __restrict__ x = b.x[parity];
+    const int4* __restrict__ xq = b.xq[parity];
+    const double4 xi = x[i];
+    const int4 qi = xq[i];
+    int cx, cy, cz;
+    cell_coords(g, xi.x, xi.y, xi.z, cx, cy, cz);
+    const int kc = g.kc, nx = g.nc[0], side = 2 * kc + 1, cap = g.cap;
+    // lane v: the first or second contiguous range of stencil row v / 2
+    int pa = 0, len = 0;
+    if (lane < 2 * side * side) {
+        const int r = lane >> 1, pc = lane & 1, oz = r / side - kc, oy = r % side - kc;
+        const float gz = cell_gap(oz, (float)(xi.z - cz * g.h[2]), (float)g.h[2]);
+        const float gy = cell_gap(oy, (float)(xi.y - cy * g.h[1]), (float)g.h[1]);
+        if (gz * gz + gy * gy <= g.rv2hi) {
+            const int nz = wrapc(cz + oz, g.nc[2]), ny = wrapc(cy + oy, g.nc[1]);
+            const int64_t rowc = ((int64_t)nz * g.nc[1] + ny) * nx;
+            const int l = wrapc(cx - kc, nx), h = l + 2 * kc;
+            int e = 0;
+            if (h < nx) {
+                if (pc == 0) { pa = b.cstart[rowc + l]; e = b.cstart[rowc + h + 1]; }
+            } else if (pc == 0) {
+                pa = b.cstart[rowc + l]; e = b.cstart[rowc + nx];
+            } else {
+                pa = b.cstart[rowc]; e = b.cstart[rowc + h - nx + 1];
+            }
+            len = e - pa;
+        }
+    }
+    int end = len;      // prefix of the candidates up to this range
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(end, o, 64);
+        if (lane >= o) end += y;
+    }
+    const int total = __builtin_amdgcn_readlane(end, 63);
+    uint64_t todo = __ballot(len > 0);
+    int32_t* __restrict__ nlrow = b.nl + nl_base(i, cap);
+    int cnt = 0;
+    for (int c0 = 0; c0 < total; c0 += 64) {
+        // candidate c0 + lane: the range that holds it
+        int j = i;
+        uint64_t rest = todo;
+        while (rest) {
+            const int v = __ffsll((unsigned long long)rest) - 1;
+            rest &= rest - 1;
+            const int hi = __builtin_amdgcn_readlane(end, v), lo = hi - __builtin_amdgcn_readlane(len, v);
+            if (lo >= c0 + 64) break;
+            if (hi <= c0 + 64) todo &= ~(1ull << v);    // ends in this chunk
+            const int c = c0 + lane;
+            if (c >= lo && c < hi) j = __builtin_amdgcn_readlane(pa, v) + c - lo;
+        }
+        const int4 q = xq[j];
+        const float dx = qdiff(q.x, qi.x, g.ql[0]), dy = qdiff(q.y, qi.y, g.ql[1]), dz = qdiff(q.z, qi.z, g.ql[2]);
+        const float r2 = dx * dx + dy * dy + dz * dz;
+        bool in = j != i && r2 < g.rv2lo;
+        if (j != i && r2 >= g.rv2lo && r2 < g.rv2hi) in = exact_r2(g, xi, x[j]) < g.rv2;
+        const uint64_t m = __ballot(in);
+        const int pos = cnt + (int)__popcll(m & ((1ull << lane) - 1));
+        if (in && pos < cap) nlrow[nl_off(pos)] = j;
+        cnt += (int)__popcll(m);
+    }
+    if (lane == 0) b.ncount[i] = cnt;
+    const int k = cnt + lane;   // padding to a multiple of 8 with the particle itself
+    if (k < ((cnt + 7) & ~7) && k < cap) nlrow[nl_off(k)] = i;
+    if (bonded) {
+        // remap_bonded, a lane per bond and angle
+        const int32_t t = b.tag[i];
+        const int tc = b.tcnt_t[t];
+        if (lane == 0) b.tcnt_s[i] = tc;
+        if (lane < (tc & 0xff)) b.bp_s[(int64_t)lane * n + i] = b.inv[b.bp_t[(int64_t)lane * n + t]];
+        const int a = lane - 32;
+        if (a >= 0 && a < (tc >> 8)) {
+            const int2 e = b.ang_t[(int64_t)a * n + t];
+            const int role = (int)((uint32_t)e.x >> 30);
+            b.ang_s[(int64_t)a * n + i] = make_int2(b.inv[e.x & 0x3fffffff] | (role << 30), b.inv[e.y]);
+        }
+    }
+    nl_epilogue(b, cnt, cnt > cap);
 }
 
 // ------------------------------------------------------------------ Lees-Edwards shear
@@ -1762,10 +1908,10 @@ __device__ __forceinline__ bool finalize_block(const StepArgs& a, int& blk, int&
 
 // FP64 pair path: FP64 positions gathered from the double-buffered double4
 // array, all pair and bonded math in FP64.
-template <bool SINGLE, bool BONDED>
-__global__ void __launch_bounds__(kBlock) k_step64(const StepArgs a) {
+template <bool SINGLE, bool BONDED, int BS>
+__global__ void __launch_bounds__(BS) k_step64(const StepArgs a) {
     int blk, grid;
-    if (finalize_block(a, blk, grid)) return;
+    if (finalize_block<BS>(a, blk, grid)) return;
     const Geom& g = a.g;
     const Bufs& b = a.b;
     const int64_t n = g.n;
@@ -1775,10 +1921,10 @@ __global__ void __launch_bounds__(kBlock) k_step64(const StepArgs a) {
     for (int k = 0; k < kNacc; ++k) acc[k] = 0.0;
     bool flag_reb = false, flag_bond = false, flag_nf = false;
     const bool tensor = a.tensor != 0;
-    const int64_t ntile = (n + kBlock - 1) / kBlock;
+    const int64_t ntile = (n + BS - 1) / BS;
     const int64_t bt = xcd_block(blk, grid);
     for (int64_t t = bt * ntile / grid; t < (bt + 1) * ntile / grid; ++t) {
-    const int64_t i = t * kBlock + threadIdx.x;
+    const int64_t i = t * BS + threadIdx.x;
     if (i < n) {
         const double4 xi = xin[i];
         const int ti = SINGLE ? 0 : (int)xi.w;
@@ -1824,7 +1970,7 @@ __global__ void __launch_bounds__(kBlock) k_step64(const StepArgs a) {
         finish_particle(a, i, xi, SINGLE ? 0 : ti, F, acc, flag_reb, flag_nf);
     }
     }
-    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
+    block_epilogue<BS>(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
 }
 
 // FP32 pair path.  Neighbours are gathered as 16-byte fixed-point records;
@@ -1834,10 +1980,10 @@ __global__ void __launch_bounds__(kBlock) k_step64(const StepArgs a) {
 // from the FP64 positions, so the set of interacting pairs is that of the
 // FP64 definition.  Neighbour indices are loaded one batch of 8 ahead of
 // the gathers that use them.
-template <bool SINGLE, bool BONDED, bool TENSOR>
-__global__ void __launch_bounds__(kBlock) k_step_q(const StepArgs a) {
+template <bool SINGLE, bool BONDED, bool TENSOR, int BS>
+__global__ void __launch_bounds__(BS) k_step_q(const StepArgs a) {
     int blk, grid;
-    if (finalize_block(a, blk, grid)) return;
+    if (finalize_block<BS>(a, blk, grid)) return;
     const Geom& g = a.g;
     const Bufs& b = a.b;
     const int64_t n = g.n;
@@ -1847,10 +1993,10 @@ __global__ void __launch_bounds__(kBlock) k_step_q(const StepArgs a) {
 #pragma unroll
     for (int k = 0; k < kNacc; ++k) acc[k] = 0.0;
     bool flag_reb = false, flag_bond = false, flag_nf = false;
-    const int64_t ntile = (n + kBlock - 1) / kBlock;
+    const int64_t ntile = (n + BS - 1) / BS;
     const int64_t bt = xcd_block(blk, grid);
     for (int64_t t = bt * ntile / grid; t < (bt + 1) * ntile / grid; ++t) {
-    const int64_t i = t * kBlock + threadIdx.x;
+    const int64_t i = t * BS + threadIdx.x;
     if (i < n) {
         const double4 xi = x64[i];
         const int4 qi = quantize4(g, xi.x, xi.y, xi.z, xi.w);  // equals xq[i]: same function
@@ -1952,7 +2098,7 @@ __global__ void __launch_bounds__(kBlock) k_step_q(const StepArgs a) {
         finish_particle(a, i, xi, SINGLE ? 0 : ti, F, acc, flag_reb, flag_nf);
     }
     }
-    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : kNaccStep, blk, grid);
+    block_epilogue<BS>(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : kNaccStep, blk, grid);
 }
 
 
@@ -2158,11 +2304,11 @@ __device__ __forceinline__ float dpd_theta(uint64_t seed, uint64_t step, uint32_
 // [2][table_points] (u, f) pairs, so that their lookups do not wait on
 // global memory.  The neighbour row is pipelined: the index two slots ahead
 // and the record (and DPD velocity) one slot ahead of the pair arithmetic.
-template <bool BONDED, bool SINGLE, bool LDSTAB>
-__global__ void __launch_bounds__(kBlock) k_step_gen(const StepArgs a) {
+template <bool BONDED, bool SINGLE, bool LDSTAB, int BS>
+__global__ void __launch_bounds__(BS) k_step_gen(const StepArgs a) {
     extern __shared__ float2 stab[];
     int blk, grid;
-    if (finalize_block(a, blk, grid)) return;
+    if (finalize_block<BS>(a, blk, grid)) return;
     const Geom& g = a.g;
     const Bufs& b = a.b;
     const int64_t n = g.n;
@@ -2172,7 +2318,7 @@ __global__ void __launch_bounds__(kBlock) k_step_gen(const StepArgs a) {
         const int np = g.table_points;
         const float2* __restrict__ src0 = b.tab;
         const float2* __restrict__ src1 = b.tab + (int64_t)kCgTableRow * np;
-        for (int k = threadIdx.x; k < np; k += kBlock) {
+        for (int k = threadIdx.x; k < np; k += BS) {
             stab[k] = src0[k];
             stab[np + k] = src1[k];
         }
@@ -2195,7 +2341,7 @@ __global__ void __launch_bounds__(kBlock) k_step_gen(const StepArgs a) {
         les.drift = fabs(g.le_rate_Ly * ((double)(step + 1 - b.ctl->build_step) * g.le_dt));
     }
     const bool dpd = a.dy.dpd && a.mode == MODE_STEP;
-    const int64_t i = (int64_t)xcd_block(blk, grid) * kBlock + threadIdx.x;
+    const int64_t i = (int64_t)xcd_block(blk, grid) * BS + threadIdx.x;
     if (i < n) {
         const double4 xi = x64[i];
         const int4 qi = quantize4(g, xi.x, xi.y, xi.z, xi.w);
@@ -2329,7 +2475,7 @@ __global__ void __launch_bounds__(kBlock) k_step_gen(const StepArgs a) {
         const double F[3] = {(double)fx, (double)fy, (double)fz};
         finish_particle(a, i, xi, ti, F, acc, flag_reb, flag_nf, g.le ? &les : nullptr);
     }
-    block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
+    block_epilogue<BS>(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
 }
 
 // Step of the surrogate mode, one 256-particle tile per block: the
@@ -2722,15 +2868,22 @@ hipError_t launch_rebuild(const Geom& g, const Bufs& b, int parity, int bonded, 
     // against 512 (2M-bead melt, binning and sort per step) 62.0 -> 56.4 us,
     // and one block per 256 particles 59.2 us
     const int gs = grid_for(g.n, 2048);
+    if (g.n <= kSmallSort && g.ncell <= kSmallCells) {
+        hipLaunchKernelGGL(k_sort_small, dim3(1), dim3(kSmallBlock), 0, s, g, b, parity, bonded, advance);
+    } else {
     hipLaunchKernelGGL(k_bin, dim3(gs), dim3(kBlock), 0, s, g, b, parity, advance);
     hipLaunchKernelGGL(k_scan_chunks, dim3(kScanBlocks), dim3(kBlock), 0, s, g, b, parity);
     hipLaunchKernelGGL(k_scatter, dim3(gs), dim3(kBlock), 0, s, g, b, parity);
     hipLaunchKernelGGL(k_rank_permute, dim3(gs), dim3(kBlock), 0, s, g, b, parity);
     hipLaunchKernelGGL(k_commit, dim3(gs), dim3(kBlock), 0, s, g, b, parity, bonded);
+    }
     if (ev_sorted) (void)hipEventRecord(ev_sorted, s);
     const int64_t nt = (g.n + kTile - 1) / kTile;
     const dim3 tiles((unsigned)(nt < kNlGrid ? nt : kNlGrid));
-    if (g.nl_mat && g.le)
+    if (g.nl_wave)
+        hipLaunchKernelGGL(k_nl_wave, dim3((unsigned)((g.n + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0, s, g, b,
+                           parity, bonded);
+    else if (g.nl_mat && g.le)
         hipLaunchKernelGGL(k_nl_mtile<true>, tiles, dim3(kTile), 0, s, g, b, parity, bonded);
     else if (g.nl_mat)
         hipLaunchKernelGGL(k_nl_mtile<false>, tiles, dim3(kTile), 0, s, g, b, parity, bonded);
@@ -2741,15 +2894,14 @@ hipError_t launch_rebuild(const Geom& g, const Bufs& b, int parity, int bonded, 
     return hipGetLastError();
 }
 
-int step_launch_grid(const StepArgs& a, int fp64, int block) {
-    if (a.dy.gen || fp64 || !a.use_fast || block == kBlock) return step_grid(a.g.n);
-    const int64_t t = (a.g.n + block - 1) / block;
+int step_launch_grid(int64_t n, int block) {
+    const int64_t t = (n + block - 1) / block;
     return (int)(t < 1 ? 1 : t);
 }
 
 template <bool BONDED, bool TENSOR>
 static void launch_fast(const StepArgs& a, int block, hipStream_t s) {
-    const dim3 grid((unsigned)(step_launch_grid(a, 0, block) + a.fin)), blk((unsigned)block);
+    const dim3 grid((unsigned)(step_launch_grid(a.g.n, block) + a.fin)), blk((unsigned)block);
 #define MD_LF(BS)                                                                                  \
     do {                                                                                           \
         if (BONDED) hipLaunchKernelGGL((k_step_fast_bonded<TENSOR, BS>), grid, blk, 0, s, a);     \
@@ -2773,14 +2925,19 @@ __global__ void __launch_bounds__(kBlock) k_snapshot_v(const Bufs b, int64_t n) 
 }
 
 hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded, int block, hipStream_t s) {
-    dim3 grid((unsigned)(step_grid(a.g.n) + a.fin)), blk(kBlock);
+    const dim3 grid((unsigned)(step_launch_grid(a.g.n, block) + a.fin)), blk((unsigned)block);
+    const bool w64 = block == 64;
     if (a.dy.gen && a.dy.dpd && a.mode == MODE_STEP)
         hipLaunchKernelGGL(k_snapshot_v, dim3(grid_for(a.g.n)), dim3(kBlock), 0, s, a.b, a.g.n);
     if (a.dy.gen) {
         // tables in LDS for one particle type, when both rows fit in 32 KB
         const size_t tab_lds = 2 * sizeof(float2) * (size_t)a.g.table_points;
         const bool lds = single_type && a.b.tab && a.g.table_points >= 2 && tab_lds <= 32768;
-#define MD_LG(B, S, T) hipLaunchKernelGGL((k_step_gen<B, S, T>), grid, blk, T ? tab_lds : 0, s, a)
+#define MD_LG(B, S, T)                                                                                     \
+    do {                                                                                                   \
+        if (w64) hipLaunchKernelGGL((k_step_gen<B, S, T, 64>), grid, blk, T ? tab_lds : 0, s, a);          \
+        else hipLaunchKernelGGL((k_step_gen<B, S, T, kBlock>), grid, blk, T ? tab_lds : 0, s, a);          \
+    } while (0)
         if (bonded) {
             if (lds) MD_LG(true, true, true);
             else if (single_type) MD_LG(true, true, false);
@@ -2792,7 +2949,11 @@ hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded,
         }
 #undef MD_LG
     } else if (fp64) {
-#define MD_L64(S, B) hipLaunchKernelGGL((k_step64<S, B>), grid, blk, 0, s, a)
+#define MD_L64(S, B)                                                                  \
+    do {                                                                              \
+        if (w64) hipLaunchKernelGGL((k_step64<S, B, 64>), grid, blk, 0, s, a);        \
+        else hipLaunchKernelGGL((k_step64<S, B, kBlock>), grid, blk, 0, s, a);        \
+    } while (0)
         if (single_type) { if (bonded) MD_L64(true, true); else MD_L64(true, false); }
         else { if (bonded) MD_L64(false, true); else MD_L64(false, false); }
 #undef MD_L64
@@ -2806,7 +2967,11 @@ hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded,
             else launch_fast<false, false>(a, block, s);
         }
     } else {
-#define MD_LQ(S, B, T) hipLaunchKernelGGL((k_step_q<S, B, T>), grid, blk, 0, s, a)
+#define MD_LQ(S, B, T)                                                                   \
+    do {                                                                                 \
+        if (w64) hipLaunchKernelGGL((k_step_q<S, B, T, 64>), grid, blk, 0, s, a);        \
+        else hipLaunchKernelGGL((k_step_q<S, B, T, kBlock>), grid, blk, 0, s, a);        \
+    } while (0)
         const bool t = a.tensor != 0;
         if (single_type) {
             if (bonded) { if (t) MD_LQ(true, true, true); else MD_LQ(true, true, false); }

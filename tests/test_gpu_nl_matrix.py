@@ -33,6 +33,34 @@ def test_rows_equal_the_per_particle_build(n, side, cf, shape):
         assert np.array_equal(x, y)
 
 
+# the one-wavefront-per-particle build of small systems: one and several chunks
+# of 64 candidates, wrapped ranges, three-cell boxes, the padding's edges, bonds;
+# and the one-block sort on both sides of its limit
+@pytest.mark.parametrize("n,L,cf", [(1, 4.3, 1), (9, 4.3, 1), (300, 4.3, 1), (2000, 5.7, 1), (1000, 4.3, 2),
+                                    (4096, 14.0, 1), (4097, 14.0, 1), (20000, 21.0, 1), (500, 60.0, 1)])
+def test_small_builds_equal_the_per_particle_build(n, L, cf):
+    pos = inputs.random_positions(n, [L] * 3, seed=n)
+    kw = dict(pair={(0, 0): lj_pair(rc=1.1)}, skin=0.3, cell_factor=cf, nl_capacity=512)
+    a = rows(pos, [L] * 3, 0, **kw)
+    b = rows(pos, [L] * 3, md.MD_CFG_NL_PER_PARTICLE, **kw)
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
+
+
+def test_small_bonded_trajectory_equals_the_per_particle_build():
+    w = inputs.lattice_melt(20, 50, 0.85, seed=5)
+    got = []
+    for flags in (0, md.MD_CFG_NL_PER_PARTICLE):
+        s = System(w["pos"], w["box"], inputs.maxwell_boltzmann(1000, 1.0, seed=5), pair={(0, 0): lj_pair(rc=2 ** (1 / 6))},
+                   bonds=w["bonds"], angles=w["angles"], k_bend=1.5, dt=0.01, integrator="langevin", gamma=0.5, seed=5,
+                   flags=flags)
+        s.step(40)
+        assert s.observables()["n_rebuilds"] > 4
+        got.append(s.get_state())
+        s.close()
+    assert np.array_equal(got[0]["pos"], got[1]["pos"]) and np.array_equal(got[0]["vel"], got[1]["vel"])
+
+
 def test_pairs_at_the_list_radius():
     """Pairs placed exactly at the list radius and one ulp to either side are
     decided in FP64 (strictly inside)."""
