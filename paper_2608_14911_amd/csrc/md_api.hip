@@ -571,8 +571,8 @@ static int block_of(md_handle h) {
 // Force stage: the plain fused kernel, or the surrogate's network stage
 // followed by its fused pair-force + bonded + integration kernel.  BF16
 // form: descriptors and the matrix-core network in one kernel, the input
-// gradients passed on as BF16 rows.  FP32 form: descriptor rows, then the
-// FP32 network.  *spart receives the network's energy partials (one row),
+// gradients passed on as BF16 rows.  FP32 form: descriptor rows, the FP32
+// network, the pair force, and the rest of the step.  *spart receives the network's energy partials (one row),
 // or nullptr.
 // defer: the previous step's record is written by this stage's step kernel.
 static hipError_t launch_force_stage(md_handle h, int mode, int tensor, double* f_out, const double** spart,
@@ -593,6 +593,8 @@ static hipError_t launch_force_stage(md_handle h, int mode, int tensor, double* 
     } else {
         if ((e = launch_sur_desc2(h->g, h->b, s, h->sc, h->parity, 0, h->stream)) != hipSuccess) return e;
         if ((e = launch_sur_mlp(s, s.G, h->g.n, s.a, nullptr, epart, 0, h->step_grid, h->stream)) != hipSuccess)
+            return e;
+        if ((e = launch_sur_force(h->g, h->b, s, h->sc, h->parity, nullptr, 0.0, tensor, h->stream)) != hipSuccess)
             return e;
     }
     *spart = epart;
@@ -1357,9 +1359,7 @@ md_status md_sur_mlp_eval(md_handle h, const float* G, int64_t P, float* e, floa
         HIP_TRY(h, launch_sur_mlp16(h->sb, G, P, dedg, e, h->stream));
         return MD_OK;
     }
-    const int64_t tiles = (P + 63) / 64;
-    const int grid = (int)(tiles < 4096 ? tiles : 4096);
-    HIP_TRY(h, launch_sur_mlp(h->sb, G, P, dedg, e, nullptr, 0, grid, h->stream));
+    HIP_TRY(h, launch_sur_mlp(h->sb, G, P, dedg, e, nullptr, 0, 0, h->stream));
     return MD_OK;
 }
 
@@ -1372,7 +1372,7 @@ md_status md_sur_pair_forces(md_handle h, const float* dedg, double* f_out) {
     if ((r = rebuild_now(h, 0)) != MD_OK) return r;
     const SurBufs& s = h->sb;
     HIP_TRY(h, launch_sur_from_tag(h->g, h->b, dedg, s.a, h->stream));
-    HIP_TRY(h, launch_sur_force(h->g, h->b, s, h->sc, h->parity, nullptr, 0.0, 0, h->step_grid, h->stream));
+    HIP_TRY(h, launch_sur_force(h->g, h->b, s, h->sc, h->parity, nullptr, 0.0, 0, h->stream));
     HIP_TRY(h, launch_sur_f_to_tag(h->g, h->b, s.f, f_out, h->stream));
     return MD_OK;
 }
@@ -1398,10 +1398,9 @@ md_status md_sur_loss_grad(md_handle h, const double* frames, const double* f_re
         if ((r = rebuild_now(h, 0)) != MD_OK) return r;
         HIP_TRY(h, launch_sur_desc2(h->g, h->b, s, h->sc, 0, 0, h->stream));
         HIP_TRY(h, launch_sur_mlp(s, s.G, n, s.a, nullptr, nullptr, bf, h->step_grid, h->stream));
-        HIP_TRY(h, launch_sur_force(h->g, h->b, s, h->sc, 0, f_ref + (size_t)f * 3 * n, two_over_m, 0, h->step_grid,
-                                    h->stream));
-        HIP_TRY(h, launch_sur_loss_reduce(s, h->step_grid, f > 0, h->stream));
-        HIP_TRY(h, launch_sur_u(h->g, h->b, s, h->sc, 0, h->step_grid, h->stream));
+        HIP_TRY(h, launch_sur_force(h->g, h->b, s, h->sc, 0, f_ref + (size_t)f * 3 * n, two_over_m, 0, h->stream));
+        HIP_TRY(h, launch_sur_loss_reduce(s, sur_loss_parts(n), f > 0, h->stream));
+        HIP_TRY(h, launch_sur_u(h->g, h->b, s, h->sc, 0, h->stream));
         HIP_TRY(h, launch_sur_bwd2(s, n, bf, h->stream));
         HIP_TRY(h, launch_sur_grad_reduce(s, sur_bwd2_grid(n), f > 0, h->stream));
     }

@@ -276,13 +276,15 @@ struct SurConst {
 };
 
 hipError_t launch_sur_prepare(const SurBufs& s, hipStream_t st);
+// epart: energy partials, ncols of them (or null)
 hipError_t launch_sur_mlp(const SurBufs& s, const float* G, int64_t P, float* a, float* e, double* epart,
-                          int bf16, int grid, hipStream_t st, uint16_t* a16 = nullptr);
+                          int bf16, int ncols, hipStream_t st);
+// fref: training (delta and the loss partials, sur_loss_parts(n) of them in
+// s.part); otherwise (F, virial) in s.f and with tensor its tensor in s.u
 hipError_t launch_sur_force(const Geom& g, const Bufs& b, const SurBufs& s, const SurConst& c, int parity,
-                            const double* fref, double two_over_m, int tensor, int grid, hipStream_t st,
-                            int a_bf16 = 0);
-hipError_t launch_sur_u(const Geom& g, const Bufs& b, const SurBufs& s, const SurConst& c, int parity, int grid,
-                        hipStream_t st);
+                            const double* fref, double two_over_m, int tensor, hipStream_t st);
+int sur_loss_parts(int64_t n);
+hipError_t launch_sur_u(const Geom& g, const Bufs& b, const SurBufs& s, const SurConst& c, int parity, hipStream_t st);
 hipError_t launch_sur_bwd2(const SurBufs& s, int64_t P, int bf16, hipStream_t st);
 hipError_t launch_sur_grad_reduce(const SurBufs& s, int nblk, int accumulate, hipStream_t st);
 int sur_bwd2_grid(int64_t P);

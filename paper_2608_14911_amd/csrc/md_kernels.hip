@@ -2487,16 +2487,17 @@ __global__ void __launch_bounds__(BS) k_step_gen(const StepArgs a) {
 // ahead and the a_j rows of in-range neighbours one slot ahead of the pair
 // arithmetic that uses them.  BF16 form (A16): a rows are
 // BF16; g' is rounded to BF16 pairs and dotted with a_i and a_j by
-// v_dot2_f32_bf16 with FP32 accumulation.  FP32 form: FP32 rows and FP32
-// multiply-adds.  The pair virial goes to the step's reductions; the
-// network energy comes from the network kernel's partials.
+// v_dot2_f32_bf16 with FP32 accumulation.  FP32 form: the pair force, its
+// virial and tensor come from the pass before (s.f, s.u).  The pair virial goes
+// to the step's reductions; the network energy comes from the network
+// kernel's partials.
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 
 template <bool BONDED, bool TENSOR, bool A16>
 __global__ void __launch_bounds__(kBlock) k_sur_step(const StepArgs a, const SurBufs s, const SurConst c) {
     int blk, grid;
     if (finalize_block(a, blk, grid)) return;
-    constexpr int AW = A16 ? 16 : 32;       // 32-bit words per a row
+    constexpr int AW = 16;                  // 32-bit words per a row
     const Geom& g = a.g;
     const Bufs& b = a.b;
     const int64_t n = g.n;
@@ -2509,8 +2510,17 @@ __global__ void __launch_bounds__(kBlock) k_sur_step(const StepArgs a, const Sur
         const int4* __restrict__ xq = b.xq[a.parity];
         const double4 xi = b.x[a.parity][i];
         const int4 qi = quantize4(g, xi.x, xi.y, xi.z, xi.w);
-        const uint32_t* __restrict__ arow = A16 ? reinterpret_cast<const uint32_t*>(s.ab)
-                                                : reinterpret_cast<const uint32_t*>(s.a);
+        float fx = 0.f, fy = 0.f, fz = 0.f, wv = 0.f;
+        float txx = 0.f, tyy = 0.f, tzz = 0.f, txy = 0.f, txz = 0.f, tyz = 0.f;
+        if (!A16) {
+            const float4 f = s.f[i];
+            fx = f.x; fy = f.y; fz = f.z; wv = f.w;
+            if (TENSOR) {
+                const float* t = s.u + i * kSurNB;
+                txx = t[0]; tyy = t[1]; tzz = t[2]; txy = t[3]; txz = t[4]; tyz = t[5];
+            }
+        } else {
+        const uint32_t* __restrict__ arow = reinterpret_cast<const uint32_t*>(s.ab);
         uint32_t ai[AW];
 #pragma unroll
         for (int q = 0; q < AW / 4; ++q) {
@@ -2522,8 +2532,6 @@ __global__ void __launch_bounds__(kBlock) k_sur_step(const StepArgs a, const Sur
         const int nslots = min((cnt + 7) & ~7, g.cap);
         const int32_t* __restrict__ row = b.nl + nl_base(i, g.cap);
         const int last = nslots > 0 ? nslots - 1 : 0;
-        float fx = 0.f, fy = 0.f, fz = 0.f, wv = 0.f;
-        float txx = 0.f, tyy = 0.f, tzz = 0.f, txy = 0.f, txz = 0.f, tyz = 0.f;
         auto idx = [&](int slot) { return row[nl_off(slot < last ? slot : last)]; };
         auto geom = [&](const int4& qj, float& dx, float& dy, float& dz) {
             dx = qdiff(qj.x, qi.x, g.ql[0]);
@@ -2548,7 +2556,7 @@ __global__ void __launch_bounds__(kBlock) k_sur_step(const StepArgs a, const Sur
             sur_basis(c, r, ph);
             const float Bc = c.inv_w2 * fc;
             float cij = 0.f;
-            if (A16) {
+            {
                 // g'_k = phi_k (dfc - (r - mu_k) Bc) = phi_k (mu_k Bc + al): one
                 // FMA and one product per term (the FP32 cancellation of
                 // mu_k Bc against al is far below the BF16 rounding that follows)
@@ -2560,12 +2568,6 @@ __global__ void __launch_bounds__(kBlock) k_sur_step(const StepArgs a, const Sur
                     const bf16x2v gp = {(__bf16)g0, (__bf16)g1};
                     cij = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, ai[k2]), gp, cij, false);
                     cij = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, aj[k2]), gp, cij, false);
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < kSurNB; ++k) {
-                    const float dg = ph[k] * fmaf(-(r - c.mu[k]), Bc, dfc);
-                    cij = fmaf(__uint_as_float(ai[k]) + __uint_as_float(aj[k]), dg, cij);
                 }
             }
             const float sc = cij * __builtin_amdgcn_rcpf(r);
@@ -2610,6 +2612,7 @@ __global__ void __launch_bounds__(kBlock) k_sur_step(const StepArgs a, const Sur
                 if (inY) pair(qA, aY);
                 qA = qB; qB = qC; jA = jB; jB = jC; jC = jD;
             }
+        }
         }
         acc[A_VIR] += 0.5 * (double)wv;
         if (TENSOR) {

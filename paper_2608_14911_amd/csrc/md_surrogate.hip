@@ -10,11 +10,14 @@
 // padded image.  Every product O[p][c] = sum_k A[p][k] W[c][k] leaves its
 // result with one ownership: wavefront w holds particles 16w..16w+15, lane l
 // holds particle 16w + (l & 15) and, per 16-column block cb, the columns
-// 16 cb + 4 (l >> 4) + e, e = 0..3.  The FP32 form computes these dot
-// products on the vector ALUs; the BF16 form issues
-// v_mfma_f32_16x16x16_bf16 with the weights as the 16x16 A operand and the
-// activations as the B operand, whose accumulator layout is that same
-// ownership, so the two forms share every elementwise step.
+// 16 cb + 4 (l >> 4) + e, e = 0..3: the accumulator layout of a 16x16 matrix
+// instruction with the weights as the A operand and the activations as the B
+// operand.  The FP32 form issues v_mfma_f32_16x16x4_f32 (FP32 products and
+// sums), the BF16 form v_mfma_f32_16x16x16_bf16; the two share every
+// elementwise step.  Bound by the matrix pipe and, in the training kernel, by
+// its stages' barriers at one block per CU.  On the vector ALUs the FP32 dot
+// products waited on LDS broadcasts: 100,000 particles, forward and input
+// gradient 126 -> 40 us, double backward 540 -> 127 us.
 #include "md_device.h"
 
 namespace md {
@@ -43,9 +46,9 @@ __device__ __forceinline__ float sigm(float z) { return __builtin_amdgcn_rcpf(1.
 // ------------------------------------------------------------------ block sums
 
 // Deterministic block sum of NV doubles into part[k * gridDim.x + blockIdx.x].
-template <int NV>
+template <int NV, int BS = kBlock>
 __device__ __forceinline__ void block_store(const double* v, double* part) {
-    __shared__ double red[kBlock / 64][NV];
+    __shared__ double red[BS / 64][NV];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -60,112 +63,175 @@ __device__ __forceinline__ void block_store(const double* v, double* part) {
     }
 }
 
-// ------------------------------------------------------------------ pair force
+// ------------------------------------------------------------------ FP32 pair passes
+//
+// The descriptor, pair-force and sensitivity passes of the FP32 form and of
+// training.  Four lanes share a particle: lane group q = lane / 16 takes the
+// list slots q, q + 4, ... of particle lane % 16 of its wavefront, and the
+// groups' sums are added at the end.  One lane per particle leaves a system of
+// the training size (100,000 particles) at 1.5 wavefronts per SIMD, waiting on
+// each pair's loads; so it has six, and the passes become bound by vector ALU
+// issue.  The slot's index is loaded two turns ahead, its position one.
+// Per pass, one lane against four, 100,000 particles: descriptors 53 -> 43 us,
+// training force 155 -> 122 us, sensitivity 114 -> 74 us; pair force and
+// integration of the FP32 step 153 -> 123 + 14 us.  The force passes read a
+// 128-byte row per pair and lane, which bounds them by the L1.
 
-// F_i = sum_j ((a_i + a_j) . g'(r_ij)) (x_j - x_i) / r_ij over r_ij < r_d.
-// Inference: F into s.f, per-block virial (and tensor) partials into
-// s.part rows 1..7.  Training: delta_i = (2/M) (F_i - F_ref) into s.delta
-// and the squared residual into s.part row 8.
+constexpr int kLanes = 4;                       // lanes per particle
+constexpr int kPerWave = 64 / kLanes;           // particles per wavefront
 
-// Row of 32 input gradients: FP32, or BF16 (A16).
-template <bool A16>
-__device__ __forceinline__ void load_a(const SurBufs& s, int64_t j, float* av) {
-    if (A16) {
-        const uint4* p = reinterpret_cast<const uint4*>(s.ab + j * kSurNB);
+// Sum over the four lane groups, in every lane.
+__device__ __forceinline__ float sum_groups(float v) {
+    v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
+}
+
+// The 32 sums of a particle over the four lane groups: group q receives
+// columns 8q..8q+7 in v[0..7].
+__device__ __forceinline__ void scatter_sums(float* v) {
 #pragma unroll
-        for (int q = 0; q < kSurNB / 8; ++q) {
-            const uint4 v = p[q];
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    for (int k = 0; k < 16; ++k) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[k]), __float_as_uint(v[k + 16]), false, false);
+        v[k] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                av[8 * q + 2 * e] = bf16_to_f32(w[e] & 0xffffu);
-                av[8 * q + 2 * e + 1] = bf16_to_f32(w[e] >> 16);
-            }
-        }
-    } else {
-        const float4* p = reinterpret_cast<const float4*>(s.a + j * kSurNB);
-#pragma unroll
-        for (int q = 0; q < kSurNB / 4; ++q) {
-            const float4 v = p[q];
-            av[4 * q] = v.x; av[4 * q + 1] = v.y; av[4 * q + 2] = v.z; av[4 * q + 3] = v.w;
-        }
+    for (int k = 0; k < 8; ++k) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[k]), __float_as_uint(v[k + 8]), false, false);
+        v[k] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
 }
 
-template <bool TRAIN, bool A16>
+// fn(j, r, dx, dy, dz) for this lane's share of particle i's neighbours within r_d.
+template <typename Fn>
+__device__ __forceinline__ void for_pairs(const Geom& g, const Bufs& b, const SurConst& c, const int4* __restrict__ xq,
+                                          int64_t i, const int4& qi, Fn fn) {
+    int cnt = b.ncount[i];
+    cnt = cnt < g.cap ? cnt : g.cap;
+    const int32_t* __restrict__ row = b.nl + nl_base(i, g.cap);
+    const int q = (threadIdx.x & 63) / kPerWave, last = cnt - 1;
+    if (cnt <= 0) return;
+    int j0 = row[nl_off(min(q, last))], j1 = row[nl_off(min(q + kLanes, last))];
+    int4 q0 = xq[j0];
+    for (int k = q; k < cnt; k += kLanes) {
+        const int j = j0;
+        const int4 qj = q0;
+        j0 = j1;
+        q0 = xq[j0];
+        j1 = row[nl_off(min(k + 2 * kLanes, last))];
+        const float dx = qdiff(qj.x, qi.x, g.ql[0]);
+        const float dy = qdiff(qj.y, qi.y, g.ql[1]);
+        const float dz = qdiff(qj.z, qi.z, g.ql[2]);
+        const float r2 = dx * dx + dy * dy + dz * dz;
+        if (r2 < c.rd2 && r2 > 0.f) fn(j, sqrtf(r2), dx, dy, dz);
+    }
+}
+
+// Particle of a lane, four lanes each (XCD-aware block order); whole
+// wavefronts stay together for the sums, particles past the end idle.
+__device__ __forceinline__ int64_t shared_particle() {
+    return ((int64_t)xcd_block(blockIdx.x, gridDim.x) * (kBlock / 64) + threadIdx.x / 64) * kPerWave +
+           (threadIdx.x & (kPerWave - 1));
+}
+
+// G_k(i) = sum_j phi_k(r_ij) f_c(r_ij) into s.G.
+__global__ void __launch_bounds__(kBlock) k_sur_desc(Geom g, Bufs b, SurBufs s, SurConst c, int parity) {
+    const int64_t i = shared_particle();
+    const int4* __restrict__ xq = b.xq[parity];
+    float G[kSurNB];
+#pragma unroll
+    for (int k = 0; k < kSurNB; ++k) G[k] = 0.f;
+    if (i < g.n)
+        for_pairs(g, b, c, xq, i, xq[i], [&](int, float r, float, float, float) __attribute__((always_inline)) {
+            float dfc;
+            const float fc = sur_cutoff(c, r, dfc);
+            float ph[kSurNB];
+            sur_basis(c, r, ph);
+#pragma unroll
+            for (int k = 0; k < kSurNB; ++k) G[k] = fmaf(ph[k], fc, G[k]);
+        });
+    scatter_sums(G);
+    if (i < g.n) {
+        float4* out = reinterpret_cast<float4*>(s.G + i * kSurNB + 8 * ((threadIdx.x & 63) / kPerWave));
+        out[0] = make_float4(G[0], G[1], G[2], G[3]);
+        out[1] = make_float4(G[4], G[5], G[6], G[7]);
+    }
+}
+
+// F_i = sum_j ((a_i + a_j) . g'(r_ij)) (x_j - x_i) / r_ij over r_ij < r_d.
+// TRAIN: delta_i = (2/M) (F_i - F_ref) into s.delta and the squared residual
+// into s.part, one value per block; otherwise (F, virial) into s.f and, when
+// asked for, the virial tensor into the first six columns of s.u.
+template <bool TRAIN>
 __global__ void __launch_bounds__(kBlock) k_sur_force(Geom g, Bufs b, SurBufs s, SurConst c, int parity,
                                                      const double* __restrict__ fref, double two_over_m,
                                                      int tensor) {
-    const int64_t n = g.n;
+    const int64_t i = shared_particle();
     const int4* __restrict__ xq = b.xq[parity];
-    double acc[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) acc[k] = 0.0;
-    for (int64_t i = gtid_xcd(); i < n; i += gstride()) {
-        const int4 qi = xq[i];
+    float fx = 0.f, fy = 0.f, fz = 0.f, w = 0.f;
+    float t[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    double acc = 0.0;
+    if (i < g.n) {
         float ai[kSurNB];
-        load_a<A16>(s, i, ai);
-        int cnt = b.ncount[i];
-        cnt = cnt < g.cap ? cnt : g.cap;
-        const int32_t* __restrict__ row = b.nl + nl_base(i, g.cap);
-        float fx = 0.f, fy = 0.f, fz = 0.f, w = 0.f;
-        float txx = 0.f, tyy = 0.f, tzz = 0.f, txy = 0.f, txz = 0.f, tyz = 0.f;
-        for (int k = 0; k < cnt; ++k) {
-            const int j = row[nl_off(k)];
-            const int4 qj = xq[j];
-            const float dx = qdiff(qj.x, qi.x, g.ql[0]);
-            const float dy = qdiff(qj.y, qi.y, g.ql[1]);
-            const float dz = qdiff(qj.z, qi.z, g.ql[2]);
-            const float r2 = dx * dx + dy * dy + dz * dz;
-            if (r2 < c.rd2 && r2 > 0.f) {
-                const float r = sqrtf(r2);
-                float dfc;
-                const float fc = sur_cutoff(c, r, dfc);
-                float av[kSurNB];
-                load_a<A16>(s, j, av);
-                float ph[kSurNB];
-                sur_basis(c, r, ph);
-                // g'_k = phi_k (f_c' - (r - mu_k) f_c / w^2): one subtract, two
-                // fused multiply-adds and a multiply per basis function
-                const float B = c.inv_w2 * fc;
-                float cij = 0.f;
+        auto load_a = [&](int64_t j, float* v) __attribute__((always_inline)) {
+            const float4* p = reinterpret_cast<const float4*>(s.a + j * kSurNB);
 #pragma unroll
-                for (int kk = 0; kk < kSurNB; ++kk) {
-                    const float t = r - c.mu[kk];
-                    const float dg = ph[kk] * fmaf(-t, B, dfc);
-                    cij = fmaf(ai[kk] + av[kk], dg, cij);
-                }
-                const float sc = cij / r;
-                fx += sc * dx;
-                fy += sc * dy;
-                fz += sc * dz;
-                w -= cij * r;
-                if (!TRAIN && tensor) {
-                    // r_ij f_ij with r_ij = -(dx, dy, dz), f_ij = sc (dx, dy, dz)
-                    txx -= sc * dx * dx; tyy -= sc * dy * dy; tzz -= sc * dz * dz;
-                    txy -= sc * dx * dy; txz -= sc * dx * dz; tyz -= sc * dy * dz;
-                }
+            for (int q = 0; q < kSurNB / 4; ++q) {
+                const float4 u = p[q];
+                v[4 * q] = u.x; v[4 * q + 1] = u.y; v[4 * q + 2] = u.z; v[4 * q + 3] = u.w;
             }
-        }
-        if (TRAIN) {
-            const int64_t t = b.tag[i];
-            const double ex = (double)fx - fref[3 * t], ey = (double)fy - fref[3 * t + 1],
-                         ez = (double)fz - fref[3 * t + 2];
-            acc[0] += ex * ex + ey * ey + ez * ez;
-            s.delta[i] = make_float4((float)(two_over_m * ex), (float)(two_over_m * ey), (float)(two_over_m * ez), 0.f);
-        } else {
-            s.f[i] = make_float4(fx, fy, fz, 0.f);
-            acc[0] += 0.5 * (double)w;
-            if (tensor) {
-                acc[1] += 0.5 * (double)txx; acc[2] += 0.5 * (double)tyy; acc[3] += 0.5 * (double)tzz;
-                acc[4] += 0.5 * (double)txy; acc[5] += 0.5 * (double)txz; acc[6] += 0.5 * (double)tyz;
+        };
+        load_a(i, ai);
+        for_pairs(g, b, c, xq, i, xq[i], [&](int j, float r, float dx, float dy, float dz) __attribute__((always_inline)) {
+            float av[kSurNB];
+            load_a(j, av);
+            float dfc;
+            const float fc = sur_cutoff(c, r, dfc);
+            float ph[kSurNB];
+            sur_basis(c, r, ph);
+            // g'_k = phi_k (f_c' - (r - mu_k) f_c / w^2): one subtract, two
+            // fused multiply-adds and a multiply per basis function
+            const float B = c.inv_w2 * fc;
+            float cij = 0.f;
+#pragma unroll
+            for (int k = 0; k < kSurNB; ++k) cij = fmaf(ai[k] + av[k], ph[k] * fmaf(-(r - c.mu[k]), B, dfc), cij);
+            const float sc = cij / r;
+            fx += sc * dx;
+            fy += sc * dy;
+            fz += sc * dz;
+            w -= cij * r;
+            if (!TRAIN && tensor) {
+                // r_ij f_ij with r_ij = -(dx, dy, dz), f_ij = sc (dx, dy, dz)
+                t[0] -= sc * dx * dx; t[1] -= sc * dy * dy; t[2] -= sc * dz * dz;
+                t[3] -= sc * dx * dy; t[4] -= sc * dx * dz; t[5] -= sc * dy * dz;
             }
-        }
+        });
     }
+    fx = sum_groups(fx);
+    fy = sum_groups(fy);
+    fz = sum_groups(fz);
+    const bool mine = i < g.n && (threadIdx.x & 63) < kPerWave;
     if (TRAIN) {
-        block_store<1>(acc, s.part + (int64_t)8 * gridDim.x);
+        if (mine) {
+            const int64_t tg = b.tag[i];
+            const double ex = (double)fx - fref[3 * tg], ey = (double)fy - fref[3 * tg + 1],
+                         ez = (double)fz - fref[3 * tg + 2];
+            acc = ex * ex + ey * ey + ez * ez;
+            s.delta[i] = make_float4((float)(two_over_m * ex), (float)(two_over_m * ey), (float)(two_over_m * ez), 0.f);
+        }
+        block_store<1>(&acc, s.part);
     } else {
-        block_store<7>(acc, s.part + (int64_t)1 * gridDim.x);
+        w = sum_groups(w);
+        if (mine) s.f[i] = make_float4(fx, fy, fz, w);
+        if (tensor) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) t[k] = sum_groups(t[k]);
+            if (mine) {
+                float2* out = reinterpret_cast<float2*>(s.u + i * kSurNB);
+                out[0] = make_float2(t[0], t[1]);
+                out[1] = make_float2(t[2], t[3]);
+                out[2] = make_float2(t[4], t[5]);
+            }
+        }
     }
 }
 
@@ -173,43 +239,30 @@ __global__ void __launch_bounds__(kBlock) k_sur_force(Geom g, Bufs b, SurBufs s,
 // sensitivity of the loss to a_i (each a_i enters the pair terms of i as
 // the first and of its neighbours as the second index).
 __global__ void __launch_bounds__(kBlock) k_sur_u(Geom g, Bufs b, SurBufs s, SurConst c, int parity) {
-    const int64_t n = g.n;
+    const int64_t i = shared_particle();
     const int4* __restrict__ xq = b.xq[parity];
-    for (int64_t i = gtid_xcd(); i < n; i += gstride()) {
-        const int4 qi = xq[i];
+    float U[kSurNB];
+#pragma unroll
+    for (int k = 0; k < kSurNB; ++k) U[k] = 0.f;
+    if (i < g.n) {
         const float4 di = s.delta[i];
-        int cnt = b.ncount[i];
-        cnt = cnt < g.cap ? cnt : g.cap;
-        const int32_t* __restrict__ row = b.nl + nl_base(i, g.cap);
-        float U[kSurNB];
+        for_pairs(g, b, c, xq, i, xq[i], [&](int j, float r, float dx, float dy, float dz) __attribute__((always_inline)) {
+            float dfc;
+            const float fc = sur_cutoff(c, r, dfc);
+            const float4 dj = s.delta[j];
+            const float proj = ((di.x - dj.x) * dx + (di.y - dj.y) * dy + (di.z - dj.z) * dz) / r;
+            float ph[kSurNB];
+            sur_basis(c, r, ph);
+            const float B = c.inv_w2 * fc;
 #pragma unroll
-        for (int k = 0; k < kSurNB; ++k) U[k] = 0.f;
-        for (int k = 0; k < cnt; ++k) {
-            const int j = row[nl_off(k)];
-            const int4 qj = xq[j];
-            const float dx = qdiff(qj.x, qi.x, g.ql[0]);
-            const float dy = qdiff(qj.y, qi.y, g.ql[1]);
-            const float dz = qdiff(qj.z, qi.z, g.ql[2]);
-            const float r2 = dx * dx + dy * dy + dz * dz;
-            if (r2 < c.rd2 && r2 > 0.f) {
-                const float r = sqrtf(r2);
-                float dfc;
-                const float fc = sur_cutoff(c, r, dfc);
-                const float4 dj = s.delta[j];
-                const float proj = ((di.x - dj.x) * dx + (di.y - dj.y) * dy + (di.z - dj.z) * dz) / r;
-                float ph[kSurNB];
-                sur_basis(c, r, ph);
-                const float B = c.inv_w2 * fc;
-#pragma unroll
-                for (int q = 0; q < kSurNB; ++q) {
-                    const float t = r - c.mu[q];
-                    U[q] = fmaf(proj * ph[q], fmaf(-t, B, dfc), U[q]);
-                }
-            }
-        }
-        float4* out = reinterpret_cast<float4*>(s.u + i * kSurNB);
-#pragma unroll
-        for (int q = 0; q < kSurNB / 4; ++q) out[q] = make_float4(U[4 * q], U[4 * q + 1], U[4 * q + 2], U[4 * q + 3]);
+            for (int k = 0; k < kSurNB; ++k) U[k] = fmaf(proj * ph[k], fmaf(-(r - c.mu[k]), B, dfc), U[k]);
+        });
+    }
+    scatter_sums(U);
+    if (i < g.n) {
+        float4* out = reinterpret_cast<float4*>(s.u + i * kSurNB + 8 * ((threadIdx.x & 63) / kPerWave));
+        out[0] = make_float4(U[0], U[1], U[2], U[3]);
+        out[1] = make_float4(U[4], U[5], U[6], U[7]);
     }
 }
 
@@ -256,19 +309,28 @@ struct WImage<true> {
 template <int NC, int K, int SA, int SW>
 __device__ __forceinline__ void tile_gemm(const float* __restrict__ A, const float* __restrict__ W, float* out,
                                           int p, int hq) {
+    const int r = threadIdx.x & 15;
+    float4v acc[NC / 16];
 #pragma unroll
-    for (int v = 0; v < NC / 4; ++v) out[v] = 0.f;
-#pragma unroll 2
-    for (int k = 0; k < K; k += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(A + p * SA + k);
+    for (int cb = 0; cb < NC / 16; ++cb) acc[cb] = float4v{0.f, 0.f, 0.f, 0.f};
+    // v_mfma_f32_16x16x4_f32 contracts lane group q's k = q; four in a row
+    // take a 16-wide block of K as k = 4q + step, one 16-byte LDS read each side
 #pragma unroll
-        for (int cb = 0; cb < NC / 16; ++cb)
+    for (int kb = 0; kb < K / 16; ++kb) {
+        const float4 x = *reinterpret_cast<const float4*>(A + p * SA + 16 * kb + 4 * hq);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float4 wv = *reinterpret_cast<const float4*>(W + (16 * cb + 4 * hq + e) * SW + k);
-                out[4 * cb + e] += x.x * wv.x + x.y * wv.y + x.z * wv.z + x.w * wv.w;
-            }
+        for (int cb = 0; cb < NC / 16; ++cb) {
+            const float4 wv = *reinterpret_cast<const float4*>(W + (16 * cb + r) * SW + 16 * kb + 4 * hq);
+            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.x, x.x, acc[cb], 0, 0, 0);
+            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.y, x.y, acc[cb], 0, 0, 0);
+            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.z, x.z, acc[cb], 0, 0, 0);
+            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, x.w, acc[cb], 0, 0, 0);
+        }
     }
+#pragma unroll
+    for (int cb = 0; cb < NC / 16; ++cb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[4 * cb + e] = acc[cb][e];
 }
 
 template <int NC, int K, int SA, int SW>
@@ -315,17 +377,22 @@ __device__ __forceinline__ void tile_wgrad(const float* __restrict__ A, const fl
             }
         }
     } else {
+        float4v c[NM / 16];
+#pragma unroll
+        for (int mb = 0; mb < NM / 16; ++mb)
+            c[mb] = float4v{acc[4 * mb], acc[4 * mb + 1], acc[4 * mb + 2], acc[4 * mb + 3]};
 #pragma unroll 4
-        for (int p = 0; p < 64; ++p) {
-            const float4 a4 = *reinterpret_cast<const float4*>(A + p * SA + 16 * w + 4 * hq);
-            const float av[4] = {a4.x, a4.y, a4.z, a4.w};
+        for (int p0 = 0; p0 < 64; p0 += 4) {
+            const int p = p0 + hq;
+            const float av = A[p * SA + 16 * w + r];
 #pragma unroll
-            for (int mb = 0; mb < NM / 16; ++mb) {
-                const float bv = B[p * SB + 16 * mb + r];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[4 * mb + e] += av[e] * bv;
-            }
+            for (int mb = 0; mb < NM / 16; ++mb)
+                c[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, B[p * SB + 16 * mb + r], c[mb], 0, 0, 0);
         }
+#pragma unroll
+        for (int mb = 0; mb < NM / 16; ++mb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[4 * mb + e] = c[mb][e];
     }
 }
 
@@ -394,55 +461,51 @@ __device__ __forceinline__ void tile_gemm(const uint16_t* __restrict__ A, const 
     }
 }
 
-template <bool BF16>
-__device__ __forceinline__ void load_x(const SurBufs& s, const float* __restrict__ G, int64_t base, int64_t P,
-                                       typename Act<BF16>::T* sX) {
-    const int t = threadIdx.x;
-    const int p = t >> 2, c0 = (t & 3) * 8;
-    const bool ok = base + p < P;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int c = c0 + 4 * h;
-        float4 gv = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (ok) gv = *reinterpret_cast<const float4*>(G + (base + p) * kSurNB + c);
-        const float4 m = *reinterpret_cast<const float4*>(s.gmean + c);
-        const float4 is = *reinterpret_cast<const float4*>(s.gistd + c);
-        const float xv[4] = {(gv.x - m.x) * is.x, (gv.y - m.y) * is.y, (gv.z - m.z) * is.z, (gv.w - m.w) * is.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sX[p * Act<BF16>::S32 + c + e] = Act<BF16>::put(ok ? xv[e] : 0.f);
-    }
-}
-
-// Forward and input gradient on tiles of 64 rows:
+// Forward and input gradient, 16 rows per wavefront:
 //   z1 = W1 x + b1, h1 = silu(z1), z2 = W2 h1 + b2, E = w3 . silu(z2) + b3,
 //   gz2 = w3 silu'(z2), gz1 = (W2^T gz2) silu'(z1), dE/dG = (W1^T gz1) istd.
+// A wavefront's rows are its own from the load on, so the wavefronts share
+// only the weights' LDS image and never wait for each other; eight of them,
+// two per SIMD, fill the LDS with it (100,000 rows, FP32: 53 us with block-wide
+// stages and four wavefronts, 40 us so).
+constexpr int kMlpBlock = 512;
 template <bool BF16>
-__global__ void __launch_bounds__(kSB) k_sur_mlp(SurBufs s, const float* __restrict__ G, int64_t P,
-                                                 float* __restrict__ aout, float* __restrict__ eout,
-                                                 double* __restrict__ epart, uint16_t* __restrict__ aout16) {
+__global__ void __launch_bounds__(kMlpBlock) k_sur_mlp(SurBufs s, const float* __restrict__ G, int64_t P,
+                                                       float* __restrict__ aout, float* __restrict__ eout,
+                                                       double* __restrict__ epart, int ncols) {
     using AT = typename Act<BF16>::T;
-    constexpr int S32 = Act<BF16>::S32, S64 = Act<BF16>::S64;
+    constexpr int S64 = Act<BF16>::S64;
     __shared__ WImage<BF16> wi;
-    __shared__ __attribute__((aligned(16))) AT sX[64 * S32];
-    __shared__ __attribute__((aligned(16))) AT sA[64 * S64];
-    __shared__ __attribute__((aligned(16))) AT sB[64 * S64];
+    __shared__ __attribute__((aligned(16))) AT act[kMlpBlock / 64][2][16 * S64];
     wi.load(s);
     __syncthreads();   // the weight image is complete before any lane reads it
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hq = lane >> 4;
-    const int p = 16 * w + (lane & 15);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hq = lane >> 4, p = lane & 15;
+    AT* const sA = act[w][0];
+    AT* const sB = act[w][1];   // the inputs, then gz2
     const float* b1 = wi.bias();
     const float* b2 = b1 + 64;
     const float* w3 = b1 + 128;
     const float b3 = b1[192];
     double esum = 0.0;
-    const int64_t ntile = (P + 63) / 64;
-    for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-        const int64_t base = tile * 64;
-        __syncthreads();   // previous tile done with sX/sA/sB
-        load_x<BF16>(s, G, base, P, sX);
-        __syncthreads();
+    const int64_t ntile = (P + 15) / 16, nwave = (int64_t)gridDim.x * (kMlpBlock / 64);
+    for (int64_t tile = (int64_t)blockIdx.x * (kMlpBlock / 64) + w; tile < ntile; tile += nwave) {
+        const int64_t base = tile * 16;
+        const bool valid = base + p < P;
+        // row p, columns 8 hq .. 8 hq + 7, standardised
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int c = 8 * hq + 4 * h;
+            float4 gv = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (valid) gv = *reinterpret_cast<const float4*>(G + (base + p) * kSurNB + c);
+            const float4 m = *reinterpret_cast<const float4*>(s.gmean + c);
+            const float4 is = *reinterpret_cast<const float4*>(s.gistd + c);
+            const float xv[4] = {(gv.x - m.x) * is.x, (gv.y - m.y) * is.y, (gv.z - m.z) * is.z, (gv.w - m.w) * is.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sB[p * S64 + c + e] = Act<BF16>::put(valid ? xv[e] : 0.f);
+        }
+        __builtin_amdgcn_wave_barrier();
         float z[16], s1[16];
-        tile_gemm<64, 32, S32, BF16 ? kSW1 : kPF1>(sX, wi.W1(), z, p, hq);
+        tile_gemm<64, 32, S64, BF16 ? kSW1 : kPF1>(sB, wi.W1(), z, p, hq);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int h = 16 * (v >> 2) + 4 * hq + (v & 3);
@@ -451,7 +514,7 @@ __global__ void __launch_bounds__(kSB) k_sur_mlp(SurBufs s, const float* __restr
             s1[v] = sg * (1.f + zz * (1.f - sg));
             sA[p * S64 + h] = Act<BF16>::put(zz * sg);
         }
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
         tile_gemm<64, 64, S64, BF16 ? kSW64 : kPF64>(sA, wi.W2(), z, p, hq);
         float e = 0.f;
 #pragma unroll
@@ -464,19 +527,18 @@ __global__ void __launch_bounds__(kSB) k_sur_mlp(SurBufs s, const float* __restr
         }
         e += __shfl_xor(e, 16, 64);
         e += __shfl_xor(e, 32, 64);
-        const bool valid = base + p < P;
         if (hq == 0 && valid) {
             if (eout) eout[base + p] = e + b3;
             esum += (double)(e + b3);
         }
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
         tile_gemm<64, 64, S64, BF16 ? kSW64 : kPF64>(sB, wi.W2T(), z, p, hq);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int h = 16 * (v >> 2) + 4 * hq + (v & 3);
             sA[p * S64 + h] = Act<BF16>::put(z[v] * s1[v]);
         }
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
         float gx[8];
         tile_gemm<32, 64, S64, BF16 ? kSW64 : kPF64>(sA, wi.W1T(), gx, p, hq);
         if (valid) {
@@ -484,20 +546,18 @@ __global__ void __launch_bounds__(kSB) k_sur_mlp(SurBufs s, const float* __restr
             for (int cb = 0; cb < 2; ++cb) {
                 const int k0 = 16 * cb + 4 * hq;
                 const float4 is = *reinterpret_cast<const float4*>(s.gistd + k0);
-                const float4 av = make_float4(gx[4 * cb] * is.x, gx[4 * cb + 1] * is.y, gx[4 * cb + 2] * is.z,
-                                              gx[4 * cb + 3] * is.w);
-                if (aout) *reinterpret_cast<float4*>(aout + (base + p) * kSurNB + k0) = av;
-                if (aout16) {
-                    const uint32_t lo = (uint16_t)bf16_rne(av.x) | ((uint32_t)(uint16_t)bf16_rne(av.y) << 16);
-                    const uint32_t hi = (uint16_t)bf16_rne(av.z) | ((uint32_t)(uint16_t)bf16_rne(av.w) << 16);
-                    *reinterpret_cast<uint2*>(aout16 + (base + p) * kSurNB + k0) = make_uint2(lo, hi);
-                }
+                *reinterpret_cast<float4*>(aout + (base + p) * kSurNB + k0) =
+                    make_float4(gx[4 * cb] * is.x, gx[4 * cb + 1] * is.y, gx[4 * cb + 2] * is.z, gx[4 * cb + 3] * is.w);
             }
         }
+        __builtin_amdgcn_wave_barrier();
     }
     if (epart) {
-        __syncthreads();
-        block_store<1>(&esum, epart);
+        // one column per block; the grid's columns past it hold nothing
+        for (int c = (int)(blockIdx.x + gridDim.x) + (int)threadIdx.x * (int)gridDim.x; c < ncols;
+             c += kMlpBlock * (int)gridDim.x)
+            epart[c] = 0.0;
+        block_store<1, kMlpBlock>(&esum, epart);
     }
 }
 
@@ -617,21 +677,47 @@ __global__ void __launch_bounds__(kSB) k_sur_bwd2(SurBufs s, int64_t P) {
     if (threadIdx.x == 192) out[kOB3] = 0.f;
 }
 
-// grad[k] (+)= sum over blocks of gpart[blk][k], in block order.
+// grad[k] (+)= sum over blocks of gpart[blk][k]: 64 parameters per block, each
+// wavefront a quarter of the rows in order, then the four quarters in order
+// (one thread per parameter over all rows: 62 us, 5 us so).
+constexpr int kGradCols = 64;
 __global__ void __launch_bounds__(kBlock) k_sur_grad_reduce(SurBufs s, int nblk, int accumulate) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= kSurNP) return;
+    __shared__ float part[kBlock / 64][kGradCols];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, k = blockIdx.x * kGradCols + lane;
+    const int per = (nblk + 3) / 4, b0 = min(w * per, nblk), b1 = min(b0 + per, nblk);
     float t = 0.f;
-    for (int b = 0; b < nblk; ++b) t += s.gpart[(int64_t)b * kSurNPpad + k];
-    s.grad[k] = accumulate ? s.grad[k] + t : t;
+    if (k < kSurNP) {
+        int b = b0;
+        for (; b + 8 <= b1; b += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = s.gpart[(int64_t)(b + u) * kSurNPpad + k];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t += v[u];
+        }
+        for (; b < b1; ++b) t += s.gpart[(int64_t)b * kSurNPpad + k];
+    }
+    part[w][lane] = t;
+    __syncthreads();
+    if (w == 0 && k < kSurNP) {
+        t = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+        s.grad[k] = accumulate ? s.grad[k] + t : t;
+    }
 }
 
-// loss (+)= sum of the loss partials, in block order.
-__global__ void k_sur_loss_reduce(SurBufs s, int grid, int accumulate) {
-    if (threadIdx.x != 0) return;
+// loss (+)= sum of the loss partials, by one block in a fixed order.
+__global__ void __launch_bounds__(kBlock) k_sur_loss_reduce(SurBufs s, int grid, int accumulate) {
+    __shared__ double red[kBlock / 64];
     double t = 0.0;
-    for (int b = 0; b < grid; ++b) t += s.part[(int64_t)8 * grid + b];
-    s.loss[0] = accumulate ? s.loss[0] + t : t;
+    for (int b = threadIdx.x; b < grid; b += kBlock) t += s.part[b];
+    t = wave_sum(t);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        t = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) t += red[w];
+        s.loss[0] = accumulate ? s.loss[0] + t : t;
+    }
 }
 
 // Adam (Kingma and Ba 2015) on the master weights, then nothing else: the
@@ -961,12 +1047,11 @@ __device__ __forceinline__ void desc_row(const Geom& g, const Bufs& b, const Sur
     }
 }
 
-// Descriptors of one 256-particle tile per block (XCD-aware block order).
-// NET = false: the FP32 rows go to s.G.  NET = true: each wavefront runs the
-// BF16 network on its 64 particles straight from registers and LDS, writes
+// Descriptors of one 256-particle tile per block (XCD-aware block order) and
+// the BF16 network: each wavefront runs it on its 64 particles straight from
+// registers and LDS, writes
 // the BF16 input gradients a_i to s.ab and the block's energy sum to
 // epart; the descriptors never reach HBM.
-template <bool NET>
 __global__ void __launch_bounds__(kBlock) k_sur_desc2(Geom g, Bufs b, SurBufs s, SurConst c, int parity,
                                                      double* __restrict__ epart) {
     const int64_t n = g.n;
@@ -974,15 +1059,6 @@ __global__ void __launch_bounds__(kBlock) k_sur_desc2(Geom g, Bufs b, SurBufs s,
     const int64_t i = tile * kBlock + threadIdx.x;
     const bool ok = i < n;
     float G[kSurNB];
-    if (!NET) {
-        if (ok) {
-            desc_row(g, b, c, b.xq[parity], i, G);
-            float4* out = reinterpret_cast<float4*>(s.G + i * kSurNB);
-#pragma unroll
-            for (int q = 0; q < kSurNB / 4; ++q) out[q] = make_float4(G[4 * q], G[4 * q + 1], G[4 * q + 2], G[4 * q + 3]);
-        }
-        return;
-    }
     __shared__ MImage wi;
     __shared__ __attribute__((aligned(16))) uint16_t xs[kBlock / 64][64 * kXS];
     __shared__ float es[kBlock / 64][64];
@@ -1070,37 +1146,43 @@ hipError_t launch_sur_prepare(const SurBufs& s, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_sur_mlp(const SurBufs& s, const float* G, int64_t P, float* a, float* e, double* epart,
-                          int bf16, int grid, hipStream_t st, uint16_t* a16) {
+hipError_t launch_sur_mlp(const SurBufs& s, const float* G, int64_t P, float* a, float* e, double* epart, int bf16,
+                          int ncols, hipStream_t st) {
+    const int64_t rows = kMlpBlock / 64 * 16;
+    int64_t grid = (P + rows - 1) / rows;
+    if (grid > 256) grid = 256;     // one block per CU
+    if (epart && grid > ncols) grid = ncols;
     if (bf16)
-        hipLaunchKernelGGL(k_sur_mlp<true>, dim3(grid), dim3(kSB), 0, st, s, G, P, a, e, epart, a16);
+        hipLaunchKernelGGL(k_sur_mlp<true>, dim3((unsigned)grid), dim3(kMlpBlock), 0, st, s, G, P, a, e, epart, ncols);
     else
-        hipLaunchKernelGGL(k_sur_mlp<false>, dim3(grid), dim3(kSB), 0, st, s, G, P, a, e, epart, a16);
+        hipLaunchKernelGGL(k_sur_mlp<false>, dim3((unsigned)grid), dim3(kMlpBlock), 0, st, s, G, P, a, e, epart, ncols);
     return hipGetLastError();
 }
 
+// blocks of the four-lanes-per-particle passes
+static dim3 shared_grid(int64_t n) {
+    const int64_t per = kBlock / kLanes;
+    return dim3((unsigned)((n + per - 1) / per));
+}
+
+int sur_loss_parts(int64_t n) { return (int)shared_grid(n).x; }
+
 hipError_t launch_sur_force(const Geom& g, const Bufs& b, const SurBufs& s, const SurConst& c, int parity,
-                            const double* fref, double two_over_m, int tensor, int grid, hipStream_t st,
-                            int a_bf16) {
+                            const double* fref, double two_over_m, int tensor, hipStream_t st) {
     if (fref)
-        hipLaunchKernelGGL((k_sur_force<true, false>), dim3(grid), dim3(kBlock), 0, st, g, b, s, c, parity, fref,
-                           two_over_m, 0);
-    else if (a_bf16)
-        hipLaunchKernelGGL((k_sur_force<false, true>), dim3(grid), dim3(kBlock), 0, st, g, b, s, c, parity, nullptr,
-                           0.0, tensor);
+        hipLaunchKernelGGL(k_sur_force<true>, shared_grid(g.n), dim3(kBlock), 0, st, g, b, s, c, parity, fref, two_over_m, 0);
     else
-        hipLaunchKernelGGL((k_sur_force<false, false>), dim3(grid), dim3(kBlock), 0, st, g, b, s, c, parity,
-                           nullptr, 0.0, tensor);
+        hipLaunchKernelGGL(k_sur_force<false>, shared_grid(g.n), dim3(kBlock), 0, st, g, b, s, c, parity, nullptr, 0.0, tensor);
     return hipGetLastError();
 }
 
 hipError_t launch_sur_desc2(const Geom& g, const Bufs& b, const SurBufs& s, const SurConst& c, int parity, int net,
                             hipStream_t st, double* epart) {
-    const dim3 grid((unsigned)((g.n + kBlock - 1) / kBlock)), blk(kBlock);
     if (net)
-        hipLaunchKernelGGL(k_sur_desc2<true>, grid, blk, 0, st, g, b, s, c, parity, epart);
+        hipLaunchKernelGGL(k_sur_desc2, dim3((unsigned)((g.n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, g, b, s, c,
+                           parity, epart);
     else
-        hipLaunchKernelGGL(k_sur_desc2<false>, grid, blk, 0, st, g, b, s, c, parity, epart);
+        hipLaunchKernelGGL(k_sur_desc, shared_grid(g.n), dim3(kBlock), 0, st, g, b, s, c, parity);
     return hipGetLastError();
 }
 
@@ -1110,9 +1192,8 @@ hipError_t launch_sur_mlp16(const SurBufs& s, const float* G, int64_t P, float* 
     return hipGetLastError();
 }
 
-hipError_t launch_sur_u(const Geom& g, const Bufs& b, const SurBufs& s, const SurConst& c, int parity, int grid,
-                        hipStream_t st) {
-    hipLaunchKernelGGL(k_sur_u, dim3(grid), dim3(kBlock), 0, st, g, b, s, c, parity);
+hipError_t launch_sur_u(const Geom& g, const Bufs& b, const SurBufs& s, const SurConst& c, int parity, hipStream_t st) {
+    hipLaunchKernelGGL(k_sur_u, shared_grid(g.n), dim3(kBlock), 0, st, g, b, s, c, parity);
     return hipGetLastError();
 }
 
@@ -1126,13 +1207,13 @@ hipError_t launch_sur_bwd2(const SurBufs& s, int64_t P, int bf16, hipStream_t st
 }
 
 hipError_t launch_sur_grad_reduce(const SurBufs& s, int nblk, int accumulate, hipStream_t st) {
-    hipLaunchKernelGGL(k_sur_grad_reduce, dim3((kSurNP + kBlock - 1) / kBlock), dim3(kBlock), 0, st, s, nblk,
+    hipLaunchKernelGGL(k_sur_grad_reduce, dim3((kSurNP + kGradCols - 1) / kGradCols), dim3(kBlock), 0, st, s, nblk,
                        accumulate);
     return hipGetLastError();
 }
 
 hipError_t launch_sur_loss_reduce(const SurBufs& s, int grid, int accumulate, hipStream_t st) {
-    hipLaunchKernelGGL(k_sur_loss_reduce, dim3(1), dim3(64), 0, st, s, grid, accumulate);
+    hipLaunchKernelGGL(k_sur_loss_reduce, dim3(1), dim3(kBlock), 0, st, s, grid, accumulate);
     return hipGetLastError();
 }
 
