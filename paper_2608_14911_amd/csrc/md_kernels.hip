@@ -2478,6 +2478,198 @@ __global__ void __launch_bounds__(BS) k_step_gen(const StepArgs a) {
     block_epilogue<BS>(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
 }
 
+// The DPD step of one particle type (k_step_gen's arithmetic, MODE_STEP, without
+// AdResS), sheared (LE) or not.  Drawing theta_ij costs ten rounds of quarter-
+// rate multiplies, and the lanes of a wavefront draw together: walking the list
+// with the draw inside spends it on nearly every slot, though less than half
+// of a lane's slots are within the cutoffs ((1 / 1.3)^3 at skin 0.3).  So each
+// lane first collects the neighbours within the larger cutoff in LDS (kDpdQueue
+// of them at a time) and the forces walk what it collected, in list order.
+// Bound by VALU issue: 1,048,576 particles at density 3 under shear, step kernel
+// 245 -> 190 us.
+constexpr int kDpdQueue = 32;
+template <bool BONDED, bool LE, int BS>
+__global__ void __launch_bounds__(BS) k_step_dpd(const StepArgs a) {
+    extern __shared__ float2 stab[];
+    __shared__ int32_t queue[BS / 64][kDpdQueue][64];
+    int blk, grid;
+    if (finalize_block<BS>(a, blk, grid)) return;
+    const Geom& g = a.g;
+    const Bufs& b = a.b;
+    const int64_t n = g.n;
+    const int4* __restrict__ xq = b.xq[a.parity];
+    const double4* __restrict__ x64 = b.x[a.parity];
+    const float4* __restrict__ vs = reinterpret_cast<const float4*>(b.vt);
+    const int ntab = a.pt.tabn[0];
+    if (ntab > 1) {
+        for (int k = threadIdx.x; k < ntab; k += BS) stab[k] = b.tab[k];
+        __syncthreads();
+    }
+    double acc[kNacc];
+#pragma unroll
+    for (int k = 0; k < kNacc; ++k) acc[k] = 0.0;
+    bool flag_reb = false, flag_bond = false, flag_nf = false;
+    const bool tensor = a.tensor != 0;
+    const int64_t step = b.ctl->step;
+    double dw = 0.0;
+    uint32_t qd = 0;
+    LeStep les{0.0, 0.0};
+    if (LE) {
+        const double delta = le_delta(g, step);
+        dw = le_fold(g, delta);
+        qd = quantize(delta, g.qs[0]);
+        les.delta_next = le_delta(g, step + 1);
+        les.drift = fabs(g.le_rate_Ly * ((double)(step + 1 - b.ctl->build_step) * g.le_dt));
+    }
+    const int64_t i = (int64_t)xcd_block(blk, grid) * BS + threadIdx.x;
+    if (i < n) {
+        const int lane = threadIdx.x & 63;
+        int32_t(*const qu)[64] = queue[threadIdx.x >> 6];
+        const double4 xi = x64[i];
+        const int4 qi = quantize4(g, xi.x, xi.y, xi.z, xi.w);
+        const float4 vi = vs[i];
+        const DiffLEQ df{g.ql[0], g.ql[1], g.ql[2], qd};
+        // a wavefront with no particle within the list radius of the sheared
+        // boundary meets no displaced image
+        // (a thousandth more than that, for the coordinates' rounding)
+        const double rv = 1.001 * sqrt(g.rv2);
+        const bool edge = LE && __any(xi.y < rv || xi.y > g.L[1] - rv);
+        auto diff = [&](const int4& qj, float& dx, float& dy, float& dz) __attribute__((always_inline)) {
+            if (edge) return df(qi, qj, dx, dy, dz);
+            dx = qdiff(qj.x, qi.x, g.ql[0]);
+            dy = qdiff(qj.y, qi.y, g.ql[1]);
+            dz = qdiff(qj.z, qi.z, g.ql[2]);
+            return 0;
+        };
+        const float rc2lo = a.pt.rc2lo[0], rc2hi = a.pt.rc2hi[0], dpd_rc2 = a.dy.dpd_rc2;
+        const float reach2 = fmaxf(rc2hi, dpd_rc2);
+        const float irc = __builtin_amdgcn_rcpf(a.dy.dpd_rc);
+        float fx = 0.f, fy = 0.f, fz = 0.f, ue = 0.f, we = 0.f;
+        float txx = 0.f, tyy = 0.f, tzz = 0.f, txy = 0.f, txz = 0.f, tyz = 0.f;
+        int qn = 0;
+        // the collected neighbours, the next one's record and velocity ahead
+        auto forces = [&]() __attribute__((always_inline)) {
+            __builtin_amdgcn_wave_barrier();
+            int jn = qn > 0 ? qu[0][lane] : (int)i;
+            int4 qnx = xq[jn];
+            float4 vn = vs[jn];
+            for (int t = 0; t < qn; ++t) {
+                const int j = jn;
+                const int4 qj = qnx;
+                const float4 vj = vn;
+                jn = qu[min(t + 1, qn - 1)][lane];
+                qnx = xq[jn];
+                vn = vs[jn];
+                float dx, dy, dz;
+                const int s = diff(qj, dx, dy, dz);
+                const float r2 = dx * dx + dy * dy + dz * dz;
+                bool in = r2 < rc2lo;
+                if (!in && r2 < rc2hi) in = exact_r2_le(g, xi, x64[j], dw) < a.pt.rc2d[0];
+                if (in) {
+                    const PairCoef<float>& c = a.pt.f[0];
+                    float fr, u;
+                    if (ntab > 1) {
+                        const float r = sqrtf(r2);
+                        float q = (r - a.pt.tab_rmin[0]) * a.pt.tab_idr[0];
+                        q = q > 0.f ? q : 0.f;
+                        int kq = (int)q;
+                        kq = kq > ntab - 2 ? ntab - 2 : kq;
+                        const float al = q - (float)kq;
+                        const float2 t0 = stab[kq], t1 = stab[kq + 1];
+                        u = (1.f - al) * t0.x + al * t1.x;
+                        fr = ((1.f - al) * t0.y + al * t1.y) * __builtin_amdgcn_rcpf(r);
+                    } else if (c.cap2 > 0.f && r2 < c.cap2) {
+                        fr = c.fcap * __builtin_amdgcn_rsqf(r2);
+                        u = c.ucap;
+                    } else {
+                        const float inv = __builtin_amdgcn_rcpf(r2);
+                        const float s2 = c.sig2 * inv;
+                        const float s6 = s2 * s2 * s2;
+                        fr = c.eps24 * s6 * (2.f * s6 - 1.f) * inv;
+                        u = c.eps4 * s6 * (s6 - 1.f) - c.shift;
+                    }
+                    fx -= fr * dx;
+                    fy -= fr * dy;
+                    fz -= fr * dz;
+                    ue += u;
+                    we += fr * r2;
+                    if (tensor) {
+                        txx += fr * dx * dx; tyy += fr * dy * dy; tzz += fr * dz * dz;
+                        txy += fr * dx * dy; txz += fr * dx * dz; tyz += fr * dy * dz;
+                    }
+                }
+                if (r2 < dpd_rc2 && r2 > 0.f) {
+                    const float ir = __builtin_amdgcn_rsqf(r2);
+                    const float r = r2 * ir;
+                    const float w = 1.f - r * irc;
+                    const float ex = -dx * ir, ey = -dy * ir, ez = -dz * ir;
+                    // v_i - (v_j - s shear_rate Ly e_x)
+                    const float vx = vi.x - vj.x + (float)(s * g.le_rate_Ly);
+                    const float vy = vi.y - vj.y;
+                    const float vz = vi.z - vj.z;
+                    const float ev = ex * vx + ey * vy + ez * vz;
+                    const float th = dpd_theta(a.dy.seed, (uint64_t)step, __float_as_uint(vi.w), __float_as_uint(vj.w));
+                    const float A = -a.dy.dpd_gamma * w * w * ev + a.dy.dpd_sigma_isdt * w * th;
+                    fx += A * ex;
+                    fy += A * ey;
+                    fz += A * ez;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            qn = 0;
+        };
+        int cnt = b.ncount[i];
+        cnt = cnt < g.cap ? cnt : g.cap;
+        const int nslots = min((cnt + 7) & ~7, g.cap);   // padded with the particle itself
+        const int32_t* __restrict__ row = b.nl + nl_base(i, g.cap);
+        constexpr int B = 8;
+        const int last = nslots > 0 ? nslots - 1 : 0;
+        int jn[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) jn[u] = nslots > 0 ? row[nl_off(u)] : (int)i;
+        for (int k0 = 0; k0 < nslots; k0 += B) {
+            int jc[B];
+            int4 q[B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                jc[u] = jn[u];
+                q[u] = xq[jc[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                const int kk = k0 + B + u;
+                jn[u] = row[nl_off(kk < last ? kk : last)];
+            }
+            if (__any(qn > kDpdQueue - B)) forces();
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                float dx, dy, dz;
+                (void)diff(q[u], dx, dy, dz);
+                const float r2 = dx * dx + dy * dy + dz * dz;
+                qu[qn][lane] = jc[u];
+                qn += (k0 + u < cnt && r2 < reach2) ? 1 : 0;
+            }
+        }
+        forces();
+        acc[A_EPAIR] += 0.5 * (double)ue;
+        acc[A_VIR] += 0.5 * (double)we;
+        if (tensor) {
+            acc[A_TXX] += 0.5 * (double)txx; acc[A_TYY] += 0.5 * (double)tyy; acc[A_TZZ] += 0.5 * (double)tzz;
+            acc[A_TXY] += 0.5 * (double)txy; acc[A_TXZ] += 0.5 * (double)txz; acc[A_TYZ] += 0.5 * (double)tyz;
+        }
+        if (BONDED) {
+            const auto dfb = [&df](const int4& p, const int4& q, float& ddx, float& ddy, float& ddz) {
+                (void)df(p, q, ddx, ddy, ddz);
+            };
+            bonded_forces<float, int4, decltype(dfb), true>(b, a.dy, n, i, xq, qi, dfb, fx, fy, fz, acc, tensor,
+                                                            flag_bond);
+        }
+        const double F[3] = {(double)fx, (double)fy, (double)fz};
+        finish_particle(a, i, xi, 0, F, acc, flag_reb, flag_nf, LE ? &les : nullptr);
+    }
+    block_epilogue<BS>(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
+}
+
 // Step of the surrogate mode, one 256-particle tile per block: the
 // network's pair force from the per-particle input gradients a_i = dE_i/dG(i),
 //   F_i = sum_j ((a_i + a_j) . g'(r_ij)) (x_j - x_i) / r_ij  over r_ij < r_d,
@@ -2932,7 +3124,18 @@ hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded,
     const bool w64 = block == 64;
     if (a.dy.gen && a.dy.dpd && a.mode == MODE_STEP)
         hipLaunchKernelGGL(k_snapshot_v, dim3(grid_for(a.g.n)), dim3(kBlock), 0, s, a.b, a.g.n);
-    if (a.dy.gen) {
+    const size_t pair_tab = a.pt.tabn[0] > 1 ? sizeof(float2) * (size_t)a.pt.tabn[0] : 0;
+    if (a.dy.gen && a.dy.dpd && a.mode == MODE_STEP && single_type && !a.dy.adress && pair_tab <= 16384) {
+        // the queue and the pair table in LDS
+#define MD_LD(BO, LE)                                                                                     \
+    do {                                                                                                  \
+        if (w64) hipLaunchKernelGGL((k_step_dpd<BO, LE, 64>), grid, blk, pair_tab, s, a);                 \
+        else hipLaunchKernelGGL((k_step_dpd<BO, LE, kBlock>), grid, blk, pair_tab, s, a);                 \
+    } while (0)
+        if (bonded) { if (a.g.le) MD_LD(true, true); else MD_LD(true, false); }
+        else { if (a.g.le) MD_LD(false, true); else MD_LD(false, false); }
+#undef MD_LD
+    } else if (a.dy.gen) {
         // tables in LDS for one particle type, when both rows fit in 32 KB
         const size_t tab_lds = 2 * sizeof(float2) * (size_t)a.g.table_points;
         const bool lds = single_type && a.b.tab && a.g.table_points >= 2 && tab_lds <= 32768;

@@ -1,0 +1,78 @@
+"""The DPD step of one particle type collects the neighbours within reach in a
+queue of 32 per lane before it computes their forces: rows that fill it more
+than once, rows shorter than one batch of eight, a tabulated pair beside the
+thermostat, and bonds (some across the sheared boundary), in blocks of 64 and of
+256 threads.  One step from the same state and noise against the FP64 oracle's:
+a force error dF_i moves x by dt^2/(2m) dF_i and the half-step velocity by
+dt/(2m) dF_i.  |dF_i| is at most 1e-5 times the sum of the force-term
+magnitudes, and, since these forces vanish at their cutoffs, for each neighbour
+within reach the slope of its terms times the rounding of an FP32 distance
+(4 * 2^-24 of it): the table's 10 and the thermostat's
+(sigma |theta| / sqrt(dt) + gamma |v|) / rc_d at |theta| = 4, |v| = 8.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import banner, oracle_pp
+from paper_2608_14911_amd import inputs
+from paper_2608_14911_amd.system import System, lj_pair
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5
+
+
+@pytest.mark.parametrize("rho,rc_d,rate,block,table,bonded", [
+    (3.0, 1.6, 0.7, 256, False, False), (3.0, 1.6, 0.0, 64, True, False), (3.0, 1.0, 0.7, 64, False, True),
+    (0.2, 1.0, 0.7, 256, True, False), (0.01, 1.0, 0.0, 64, False, False)])
+def test_dpd_step_against_oracle(rho, rc_d, rate, block, table, bonded):
+    banner("DPD queue: rho %g, rc_d %g, rate %g, blocks of %d, table %d, bonds %d" % (
+        rho, rc_d, rate, block, table, bonded))
+    L, dt, kT, gamma = 9.0, 0.01, 1.0, 4.5
+    n = int(round(rho * L ** 3)) // 2 * 2
+    box = np.array([L, L, L])
+    pos = inputs.random_positions(n, box, seed=41)
+    kw, okw = {}, {}
+    if bonded:   # dimers along y, some of them across the sheared boundary
+        pos[1::2] = pos[0::2] + [0.0, 0.9, 0.0]
+        pos %= box
+        kw["bonds"] = okw["bonds"] = np.arange(n, dtype=np.int32).reshape(-1, 2)
+    vel = inputs.maxwell_boltzmann(n, kT, seed=41)
+    vel[:, 0] += rate * (pos[:, 1] - 0.5 * L)
+    if table:
+        kw["table_points"] = 256
+    s = System(pos, box, vel, pair={(0, 0): lj_pair(eps=0.0, rc=1.2)}, skin=0.3, dt=dt, integrator="dpd",
+               temperature=kT, gamma=gamma, seed=9, dpd_rc=rc_d, shear_rate=rate, block_size=block, **kw)
+    if table:
+        r = np.linspace(0.1, 1.2, 200)
+        u, f = 5.0 * (1.2 - r) ** 2, 10.0 * (1.2 - r)
+        s.set_pair_table(0, 0, u, f, 0.1)
+        okw["tabs"] = oracle.tables(pair={(0, 0): (0.1, u, f)})
+    pp = oracle_pp(eps=0.0, rc=1.2)
+    _, Fd, oo = oracle.forces_ext(pos, box, pp, vel=vel, shear_rate=rate, dpd_rc=rc_d, dpd_gamma=gamma, kT=kT, dt=dt,
+                                  seed=9, step=0, want_fscale=True, **okw)
+    par = dict(okw, box=box, pp=pp, ntypes=1, mass_by_type=np.array([1.0]), dt=dt, integrator=oracle.DPD,
+               temperature=kT, gamma=gamma, seed=9, dpd_rc=rc_d, shear_rate=rate)
+    st = {"pos": pos.copy(), "vel": vel.copy(), "image": np.zeros((n, 3), dtype=np.int32), "step": 0, "vel_half": 0,
+          "type": None}
+    s.step(1)
+    g = s.get_state()
+    s.close()
+    oracle.run_ext(st, par, 1)
+    dx = g["pos"] - st["pos"]
+    dx -= box * np.round(dx / box)
+    dx, dv = np.abs(dx).max(1), np.abs(g["vel"] - st["vel"]).max(1)
+    reach = max(rc_d, 1.2 if table else 0.0)
+    near = np.zeros(n)
+    for k in range(n):
+        d = pos - pos[k]
+        d -= L * np.round(d / L)   # (step 0: no shear offset yet)
+        near[k] = (np.sqrt((d * d).sum(1)) < reach).sum() - 1
+    slope = (10.0 if table else 0.0) + (4.0 * np.sqrt(2.0 * gamma * kT / dt) + 8.0 * gamma) / rc_d
+    dF = TOL * oo["fscale"] + near * slope * 4.0 * 2.0 ** -24 * reach
+    bx = dt * dt / 2 * dF + 1e-12
+    bv = dt / 2 * dF + 1e-12
+    print("%d particles: |dx| / bound %.3f, |dv| / bound %.3f, max |Fd| %.2f" % (
+        n, (dx / bx).max(), (dv / bv).max(), np.abs(Fd).max()), flush=True)
+    assert np.all(dx <= bx) and np.all(dv <= bv)
