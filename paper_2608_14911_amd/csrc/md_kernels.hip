@@ -2670,6 +2670,148 @@ __global__ void __launch_bounds__(BS) k_step_dpd(const StepArgs a) {
     block_epilogue<BS>(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
 }
 
+// The AdResS step of one particle type without shear or DPD (k_step_gen's
+// arithmetic), the pair and coarse-grained tables in LDS.  Bound by VALU issue
+// and the texture-data path together.  Records are gathered four at a time and
+// the registers held to five wavefronts per SIMD: 299,997 particles are 4,688
+// wavefronts, which four per SIMD (4,096 on the card) run in two rounds.  Step
+// kernel at that size, density 0.8442: k_step_gen 125 us; here 104 us with four
+// per SIMD and eight records, 101 with five and eight, 89-92 with five and
+// four.  Leaving out the force of weight 0 in wavefronts that need one force
+// only gained 2 us and was not worth three copies of the loop.
+template <bool BONDED, int BS>
+__global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(5))) k_step_adress(const StepArgs a) {
+    extern __shared__ float2 stab[];
+    int blk, grid;
+    if (finalize_block<BS>(a, blk, grid)) return;
+    const Geom& g = a.g;
+    const Bufs& b = a.b;
+    const int64_t n = g.n;
+    const int4* __restrict__ xq = b.xq[a.parity];
+    const double4* __restrict__ x64 = b.x[a.parity];
+    const int np = g.table_points;
+    {
+        const float2* __restrict__ src0 = b.tab;
+        const float2* __restrict__ src1 = b.tab + (int64_t)kCgTableRow * np;
+        for (int k = threadIdx.x; k < np; k += BS) {
+            stab[k] = src0[k];
+            stab[np + k] = src1[k];
+        }
+        __syncthreads();
+    }
+    double acc[kNacc];
+#pragma unroll
+    for (int k = 0; k < kNacc; ++k) acc[k] = 0.0;
+    bool flag_reb = false, flag_bond = false, flag_nf = false;
+    const bool tensor = a.tensor != 0;
+    const int64_t i = (int64_t)xcd_block(blk, grid) * BS + threadIdx.x;
+    if (i < n) {
+        const double4 xi = x64[i];
+        const int4 qi = quantize4(g, xi.x, xi.y, xi.z, xi.w);
+        const float Lx = (float)g.L[0];
+        const float rc2lo = a.pt.rc2lo[0], rc2hi = a.pt.rc2hi[0];
+        const int cgn = a.pt.cgn[0], ntab = a.pt.tabn[0];
+        const float cg_rc2lo = cgn > 1 ? a.pt.cg_rc2lo[0] : 0.f, cg_rc2hi = cgn > 1 ? a.pt.cg_rc2hi[0] : 0.f;
+        const PairCoef<float>& c = a.pt.f[0];
+        const float wi = adress_weight(a.dy, (float)xi.x, Lx);
+        float fx = 0.f, fy = 0.f, fz = 0.f, ue = 0.f, we = 0.f;
+        float txx = 0.f, tyy = 0.f, tzz = 0.f, txy = 0.f, txz = 0.f, tyz = 0.f;
+        int cnt = b.ncount[i];
+        cnt = cnt < g.cap ? cnt : g.cap;
+        const int nslots = min((cnt + 7) & ~7, g.cap);   // padded with the particle itself
+        const int32_t* __restrict__ row = b.nl + nl_base(i, g.cap);
+        // u and f = -du/dr of a row of np points, linear in r
+        auto lookup = [&](const float2* t, int nt, float rmin, float idr, float r, float& u,
+                          float& fr) __attribute__((always_inline)) {
+            float q = (r - rmin) * idr;
+            q = q > 0.f ? q : 0.f;
+            int kq = (int)q;
+            kq = kq > nt - 2 ? nt - 2 : kq;
+            const float al = q - (float)kq;
+            const float2 t0 = t[kq], t1 = t[kq + 1];
+            u = (1.f - al) * t0.x + al * t1.x;
+            fr = ((1.f - al) * t0.y + al * t1.y) * __builtin_amdgcn_rcpf(r);
+        };
+        constexpr int B = 4;
+        const int last = nslots > 0 ? nslots - 1 : 0;
+        int jn[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) jn[u] = nslots > 0 ? row[nl_off(u)] : (int)i;
+        for (int k0 = 0; k0 < nslots; k0 += B) {
+            int jc[B];
+            int4 q[B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                jc[u] = jn[u];
+                q[u] = xq[jc[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                const int kk = k0 + B + u;
+                jn[u] = row[nl_off(kk < last ? kk : last)];
+            }
+#pragma unroll
+            for (int v = 0; v < B; ++v) {
+                const float dx = qdiff(q[v].x, qi.x, g.ql[0]);
+                const float dy = qdiff(q[v].y, qi.y, g.ql[1]);
+                const float dz = qdiff(q[v].z, qi.z, g.ql[2]);
+                const float r2 = dx * dx + dy * dy + dz * dz;
+                const bool ok = k0 + v < cnt;
+                bool in = ok && r2 < rc2lo;
+                bool cg = ok && r2 < cg_rc2lo;
+                if (ok && !in && r2 < rc2hi) in = exact_r2_le(g, xi, x64[jc[v]], 0.0) < a.pt.rc2d[0];
+                if (ok && !cg && r2 < cg_rc2hi) cg = exact_r2_le(g, xi, x64[jc[v]], 0.0) < a.pt.cg_rc2d[0];
+                if (!in && !cg) continue;
+                float ucg = 0.f, frcg = 0.f, fr = 0.f, u = 0.f;
+                if (cg) lookup(stab + np, cgn, a.pt.cg_rmin[0], a.pt.cg_idr[0], sqrtf(r2), ucg, frcg);
+                if (!in) {
+                } else if (ntab > 1) {
+                    lookup(stab, ntab, a.pt.tab_rmin[0], a.pt.tab_idr[0], sqrtf(r2), u, fr);
+                } else if (c.cap2 > 0.f && r2 < c.cap2) {
+                    fr = c.fcap * __builtin_amdgcn_rsqf(r2);
+                    u = c.ucap;
+                } else {
+                    const float inv = __builtin_amdgcn_rcpf(r2);
+                    const float s2 = c.sig2 * inv;
+                    const float s6 = s2 * s2 * s2;
+                    fr = c.eps24 * s6 * (2.f * s6 - 1.f) * inv;
+                    u = c.eps4 * s6 * (s6 - 1.f) - c.shift;
+                }
+                // x_j from its fixed-point coordinate (positions lie in [0, L))
+                const float lam = wi * adress_weight(a.dy, (float)(uint32_t)q[v].x * g.ql[0], Lx);
+                u = lam * u + (1.f - lam) * ucg;
+                fr = lam * fr + (1.f - lam) * frcg;
+                fx -= fr * dx;
+                fy -= fr * dy;
+                fz -= fr * dz;
+                ue += u;
+                we += fr * r2;
+                if (tensor) {
+                    txx += fr * dx * dx; tyy += fr * dy * dy; tzz += fr * dz * dz;
+                    txy += fr * dx * dy; txz += fr * dx * dz; tyz += fr * dy * dz;
+                }
+            }
+        }
+        acc[A_EPAIR] += 0.5 * (double)ue;
+        acc[A_VIR] += 0.5 * (double)we;
+        if (tensor) {
+            acc[A_TXX] += 0.5 * (double)txx; acc[A_TYY] += 0.5 * (double)tyy; acc[A_TZZ] += 0.5 * (double)tzz;
+            acc[A_TXY] += 0.5 * (double)txy; acc[A_TXZ] += 0.5 * (double)txz; acc[A_TYZ] += 0.5 * (double)tyz;
+        }
+        if (BONDED) {
+            const DiffLEQ df{g.ql[0], g.ql[1], g.ql[2], 0u};
+            const auto dfb = [&df](const int4& p, const int4& q, float& ddx, float& ddy, float& ddz) {
+                (void)df(p, q, ddx, ddy, ddz);
+            };
+            bonded_forces<float, int4, decltype(dfb), true>(b, a.dy, n, i, xq, qi, dfb, fx, fy, fz, acc, tensor,
+                                                            flag_bond);
+        }
+        const double F[3] = {(double)fx, (double)fy, (double)fz};
+        finish_particle(a, i, xi, 0, F, acc, flag_reb, flag_nf, nullptr);
+    }
+    block_epilogue<BS>(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
+}
+
 // Step of the surrogate mode, one 256-particle tile per block: the
 // network's pair force from the per-particle input gradients a_i = dE_i/dG(i),
 //   F_i = sum_j ((a_i + a_j) . g'(r_ij)) (x_j - x_i) / r_ij  over r_ij < r_d,
@@ -3124,6 +3266,7 @@ hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded,
     const bool w64 = block == 64;
     if (a.dy.gen && a.dy.dpd && a.mode == MODE_STEP)
         hipLaunchKernelGGL(k_snapshot_v, dim3(grid_for(a.g.n)), dim3(kBlock), 0, s, a.b, a.g.n);
+    const size_t adress_tabs = 2 * sizeof(float2) * (size_t)a.g.table_points;
     const size_t pair_tab = a.pt.tabn[0] > 1 ? sizeof(float2) * (size_t)a.pt.tabn[0] : 0;
     if (a.dy.gen && a.dy.dpd && a.mode == MODE_STEP && single_type && !a.dy.adress && pair_tab <= 16384) {
         // the queue and the pair table in LDS
@@ -3135,6 +3278,15 @@ hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded,
         if (bonded) { if (a.g.le) MD_LD(true, true); else MD_LD(true, false); }
         else { if (a.g.le) MD_LD(false, true); else MD_LD(false, false); }
 #undef MD_LD
+    } else if (a.dy.gen && a.dy.adress && !a.dy.dpd && !a.g.le && single_type && a.b.tab && adress_tabs <= 32768) {
+        // both tables in LDS
+#define MD_LA(BO)                                                                                          \
+    do {                                                                                                   \
+        if (w64) hipLaunchKernelGGL((k_step_adress<BO, 64>), grid, blk, adress_tabs, s, a);                \
+        else hipLaunchKernelGGL((k_step_adress<BO, kBlock>), grid, blk, adress_tabs, s, a);                \
+    } while (0)
+        if (bonded) MD_LA(true); else MD_LA(false);
+#undef MD_LA
     } else if (a.dy.gen) {
         // tables in LDS for one particle type, when both rows fit in 32 KB
         const size_t tab_lds = 2 * sizeof(float2) * (size_t)a.g.table_points;
