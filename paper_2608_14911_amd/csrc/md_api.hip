@@ -346,7 +346,6 @@ static size_t carve(const md_config* c, const Geom& g, int step_grid, uint8_t* b
         t.cstart = (int32_t*)take(sizeof(int32_t) * (g.ncell + 1));
     }
     t.bsum = (int32_t*)take(sizeof(int32_t) * kScanBlocks * kChunkPad);
-    t.tmp = (int32_t*)take(sizeof(int32_t) * n);
     t.xt = (double4*)take(sizeof(double4) * n);
     t.vt = (double*)take(sizeof(double) * 3 * n);
     t.imgt = (int32_t*)take(sizeof(int32_t) * 3 * n);

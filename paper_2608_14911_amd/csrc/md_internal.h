@@ -136,8 +136,7 @@ struct Bufs {
     int32_t* ccount;        // [ncell], all zero between rebuilds
     int32_t* cstart;        // [ncell + 1]
     int32_t* bsum;          // [kScanBlocks] chunk sums; one system: [kScanBlocks][kChunkPad], column 0
-    int32_t* tmp;           // [N] scatter slots
-    double4* xt;            // permute temporaries
+    double4* xt;            // sort temporaries: states at their slots, unordered inside a cell
     double* vt;
     int32_t* imgt;
     int32_t* tsc;           // [N] tags in scatter order (rank inside a cell)

@@ -435,23 +435,43 @@ __global__ void __launch_bounds__(kBlock) k_scan_chunks(Geom g, Bufs b, int pari
     scan_apply_body(g, b, off);
 }
 
+// A particle's state into the sort's temporaries at a slot of its cell's segment.
+__device__ __forceinline__ void stash(const Bufs& b, int64_t n, int64_t slot, const double4& p, const double (&vv)[3],
+                                      const int32_t (&im)[3], int32_t t) {
+    b.xt[slot] = p;
+    for (int d = 0; d < 3; ++d) {
+        b.vt[d * n + slot] = vv[d];
+        b.imgt[d * n + slot] = im[d];
+    }
+    b.tsc[slot] = t;
+}
+
 // Scatter into cell segments, one atomic per run of equal cells; counts
-// return to zero for the next build.  The tags are copied beside the slots
-// so that the ranking below reads them contiguously.
-__device__ __forceinline__ void scatter_one(const Bufs& b, int64_t i, bool active) {
-    const uint32_t c = active ? b.cellid[i] : 0xffffffffu;
+// return to zero for the next build.  The whole state moves with its slot, so
+// that the pass that orders the cells reads nothing but the temporaries and
+// writes the sorted arrays at once.  A pass each for slots, order and the copy
+// back took, in the 1,048,576-particle fluid, 23 us per step on average (three
+// rebuilds in 20 steps, launches that return included); these two take 17.
+__device__ __forceinline__ void scatter_one(const Geom& g, const Bufs& b, int64_t i, bool active, int parity) {
+    const int64_t n = g.n;
+    const int64_t ii = active ? i : 0;
+    const uint32_t c = active ? b.cellid[ii] : 0xffffffffu;
+    const double4 p = b.x[parity][ii];
+    double vv[3];
+    int32_t im[3];
+    for (int d = 0; d < 3; ++d) {
+        vv[d] = b.v[d * n + ii];
+        im[d] = b.img[d * n + ii];
+    }
+    const int32_t t = b.tag[ii];
     int first, len;
     cell_run(c, active, first, len);
     const int lane = threadIdx.x & 63;
     int top = 0;
     if (active && lane == first) top = atomicSub(&b.ccount[c], len);
     top = __shfl(top, first, 64);
-    if (active) {
-        // the run owns slots [start + top - len, start + top)
-        const int slot = b.cstart[c] + top - len + (lane - first);
-        b.tmp[slot] = (int32_t)i;
-        b.tsc[slot] = b.tag[i];
-    }
+    // the run owns slots [start + top - len, start + top)
+    if (active) stash(b, n, b.cstart[c] + top - len + (lane - first), p, vv, im, t);
 }
 
 __global__ void __launch_bounds__(kBlock) k_scatter(Geom g, Bufs b, int parity) {
@@ -460,95 +480,65 @@ __global__ void __launch_bounds__(kBlock) k_scatter(Geom g, Bufs b, int parity) 
     for (int64_t k = gtid(); k < kScanBlocks; k += gstride()) b.bsum[k * kChunkPad] = 0;
     for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < g.n; i0 += gstride()) {
         const int64_t i = i0 + threadIdx.x;
-        scatter_one(b, i, i < g.n);
+        scatter_one(g, b, i, i < g.n, parity);
     }
 }
 
 // Order inside a cell by particle tag: the sorted order is then a function
 // of the positions alone, so a run resumed from a saved build snapshot
-// reproduces it exactly.  Gathers the positions, velocities and images into
-// temporaries; the tags, which no thread of this pass reads, go straight to
-// their sorted slots.
-__device__ __forceinline__ void permute_one(const Geom& g, const Bufs& b, int64_t s, int parity) {
-    const int64_t n = g.n;
-    {
-        int32_t i = b.tmp[s];
-        uint32_t c = b.cellid[i];
-        int32_t ti = b.tsc[s];
-        int st = b.cstart[c], en = b.cstart[c + 1];
-        int r = 0;
-        int u = st;
-        for (; u + 4 <= en; u += 4) {
-            const int a0 = b.tsc[u], a1 = b.tsc[u + 1], a2 = b.tsc[u + 2], a3 = b.tsc[u + 3];
-            r += (a0 < ti) + (a1 < ti) + (a2 < ti) + (a3 < ti);
-        }
-        for (; u < en; ++u) r += (b.tsc[u] < ti);
-        int64_t nw = st + r;
-        // every load before the first store: a load after a store it may
-        // alias cannot be moved above it, and would wait in turn
-        const double4 p = b.x[parity][i];
-        double vv[3];
-        int32_t im[3];
-        for (int d = 0; d < 3; ++d) {
-            vv[d] = b.v[d * n + i];
-            im[d] = b.img[d * n + i];
-        }
-        b.xt[nw] = p;
-        for (int d = 0; d < 3; ++d) {
-            b.vt[d * n + nw] = vv[d];
-            b.imgt[d * n + nw] = im[d];
-        }
-        b.tag[nw] = ti;
-    }
-}
-
-__global__ void __launch_bounds__(kBlock) k_rank_permute(Geom g, Bufs b, int parity) {
-    if (!rebuild_requested(b, parity)) return;
-    for (int64_t s = gtid(); s < g.n; s += gstride()) permute_one(g, b, s, parity);
-}
-
-__device__ __forceinline__ void commit_one(const Geom& g, const Bufs& b, int64_t s, int parity, int bonded) {
+// reproduces it exactly.  From the temporaries to the sorted arrays.
+__device__ __forceinline__ void rank_one(const Geom& g, const Bufs& b, int64_t s, int parity, int bonded) {
     const int64_t n = g.n;
     if (s == 0) {
         b.ctl->n_rebuilds += 1;
         b.ctl->nl_max = 0;
         b.ctl->build_step = b.ctl->step;
     }
-    {
-        // loads first, as in permute_one
-        const double4 p = b.xt[s];
-        double vv[3];
-        int32_t im[3];
-        for (int d = 0; d < 3; ++d) {
-            vv[d] = b.vt[d * n + s];
-            im[d] = b.imgt[d * n + s];
-        }
-        const int32_t t = bonded ? b.tag[s] : 0;
-        b.x[parity][s] = p;
-        const int4 q = quantize4(g, p.x, p.y, p.z, p.w);
-        b.xq[parity][s] = q;
-        if (g.x3_on) store_q3(b.x3[parity], s, q);
-        b.xb[s] = p.x;
-        b.xb[n + s] = p.y;
-        b.xb[2 * n + s] = p.z;
-        for (int d = 0; d < 3; ++d) {
-            b.v[d * n + s] = vv[d];
-            b.img[d * n + s] = im[d];
-        }
-        // the inverse permutation serves only the bonded remap of the list
-        // build, which also copies the per-particle bond and angle counts
-        if (bonded) b.inv[t] = (int32_t)s;
+    // every load before the first store: a load after a store it may
+    // alias cannot be moved above it, and would wait in turn
+    const double4 p = b.xt[s];
+    const int32_t t = b.tsc[s];
+    double vv[3];
+    int32_t im[3];
+    for (int d = 0; d < 3; ++d) {
+        vv[d] = b.vt[d * n + s];
+        im[d] = b.imgt[d * n + s];
     }
+    const uint32_t c = cell_of(g, p);
+    const int st = b.cstart[c], en = b.cstart[c + 1];
+    int r = 0;
+    int u = st;
+    for (; u + 4 <= en; u += 4) {
+        const int a0 = b.tsc[u], a1 = b.tsc[u + 1], a2 = b.tsc[u + 2], a3 = b.tsc[u + 3];
+        r += (a0 < t) + (a1 < t) + (a2 < t) + (a3 < t);
+    }
+    for (; u < en; ++u) r += (b.tsc[u] < t);
+    const int64_t nw = st + r;
+    b.x[parity][nw] = p;
+    const int4 q = quantize4(g, p.x, p.y, p.z, p.w);
+    b.xq[parity][nw] = q;
+    if (g.x3_on) store_q3(b.x3[parity], nw, q);
+    b.xb[nw] = p.x;
+    b.xb[n + nw] = p.y;
+    b.xb[2 * n + nw] = p.z;
+    for (int d = 0; d < 3; ++d) {
+        b.v[d * n + nw] = vv[d];
+        b.img[d * n + nw] = im[d];
+    }
+    b.tag[nw] = t;
+    // the inverse permutation serves only the bonded remap of the list
+    // build, which also copies the per-particle bond and angle counts
+    if (bonded) b.inv[t] = (int32_t)nw;
 }
 
-__global__ void __launch_bounds__(kBlock) k_commit(Geom g, Bufs b, int parity, int bonded) {
+__global__ void __launch_bounds__(kBlock) k_rank(Geom g, Bufs b, int parity, int bonded) {
     if (!rebuild_requested(b, parity)) return;
-    for (int64_t s = gtid(); s < g.n; s += gstride()) commit_one(g, b, s, parity, bonded);
+    for (int64_t s = gtid(); s < g.n; s += gstride()) rank_one(g, b, s, parity, bonded);
 }
 
 // The whole sort of a small system by one block: counts and cursors in LDS,
 // the passes separated by block barriers.  A step that rebuilds nothing then
-// launches one kernel for the sort instead of five (each launch that returns
+// launches one kernel for the sort instead of four (each launch that returns
 // costs 1.5-2.9 us), and one that does pays no launch gaps.
 constexpr int kSmallSort = 4096;    // particles
 constexpr int kSmallCells = 8192;   // cells (32 KB of LDS)
@@ -591,14 +581,18 @@ __global__ void __launch_bounds__(kSmallBlock) k_sort_small(Geom g, Bufs b, int 
     if (tid == 0) b.cstart[ncell] = n;
     __syncthreads();
     for (int i = tid; i < n; i += kSmallBlock) {
+        const double4 p = b.x[parity][i];
+        double vv[3];
+        int32_t im[3];
+        for (int d = 0; d < 3; ++d) {
+            vv[d] = b.v[(int64_t)d * n + i];
+            im[d] = b.img[(int64_t)d * n + i];
+        }
         const int slot = atomicAdd(&cnt[b.cellid[i]], 1);
-        b.tmp[slot] = i;
-        b.tsc[slot] = b.tag[i];
+        stash(b, n, slot, p, vv, im, b.tag[i]);
     }
     __syncthreads();
-    for (int s = tid; s < n; s += kSmallBlock) permute_one(g, b, s, parity);
-    __syncthreads();
-    for (int s = tid; s < n; s += kSmallBlock) commit_one(g, b, s, parity, bonded);
+    for (int s = tid; s < n; s += kSmallBlock) rank_one(g, b, s, parity, bonded);
 }
 
 // ------------------------------------------------------------------ rebuild: Verlet list
@@ -3043,25 +3037,15 @@ __global__ void __launch_bounds__(kBlock) k_batch_scatter(const SysEntry* __rest
     const TileRef r = tile_ref_spread(tab, tile_sys);
     const Bufs& b = r.e->a.b;
     if (!rebuild_requested(b, parity)) return;
-    scatter_one(b, r.i, r.i < r.e->a.g.n);
+    scatter_one(r.e->a.g, b, r.i, r.i < r.e->a.g.n, parity);
 }
 
-__global__ void __launch_bounds__(kBlock) k_batch_permute(const SysEntry* __restrict__ tab,
-                                                          const int32_t* __restrict__ tile_sys, int parity) {
+__global__ void __launch_bounds__(kBlock) k_batch_rank(const SysEntry* __restrict__ tab,
+                                                       const int32_t* __restrict__ tile_sys, int parity) {
     const TileRef r = tile_ref_spread(tab, tile_sys);
     const Bufs& b = r.e->a.b;
     if (!rebuild_requested(b, parity)) return;
-    const Geom& g = r.e->a.g;
-    if (r.i < g.n) permute_one(g, b, r.i, parity);
-}
-
-__global__ void __launch_bounds__(kBlock) k_batch_commit(const SysEntry* __restrict__ tab,
-                                                         const int32_t* __restrict__ tile_sys, int parity) {
-    const TileRef r = tile_ref_spread(tab, tile_sys);
-    const Bufs& b = r.e->a.b;
-    if (!rebuild_requested(b, parity)) return;
-    const Geom& g = r.e->a.g;
-    if (r.i < g.n) commit_one(g, b, r.i, parity, r.e->bonded);
+    if (r.i < r.e->a.g.n) rank_one(r.e->a.g, b, r.i, parity, r.e->bonded);
 }
 
 // Members whose list is built one particle per lane.
@@ -3211,8 +3195,7 @@ hipError_t launch_rebuild(const Geom& g, const Bufs& b, int parity, int bonded, 
     hipLaunchKernelGGL(k_bin, dim3(gs), dim3(kBlock), 0, s, g, b, parity, advance);
     hipLaunchKernelGGL(k_scan_chunks, dim3(kScanBlocks), dim3(kBlock), 0, s, g, b, parity);
     hipLaunchKernelGGL(k_scatter, dim3(gs), dim3(kBlock), 0, s, g, b, parity);
-    hipLaunchKernelGGL(k_rank_permute, dim3(gs), dim3(kBlock), 0, s, g, b, parity);
-    hipLaunchKernelGGL(k_commit, dim3(gs), dim3(kBlock), 0, s, g, b, parity, bonded);
+    hipLaunchKernelGGL(k_rank, dim3(gs), dim3(kBlock), 0, s, g, b, parity, bonded);
     }
     if (ev_sorted) (void)hipEventRecord(ev_sorted, s);
     const int64_t nt = (g.n + kTile - 1) / kTile;
@@ -3387,8 +3370,7 @@ hipError_t launch_batch_rebuild(const BatchCells& bc, const SysEntry* tab, const
     hipLaunchKernelGGL(k_batch_bases, dim3(1), dim3(256), 0, s, bc);
     hipLaunchKernelGGL(k_batch_localize, dim3(grid_for(bc.gg.ncell, 4096)), blk, 0, s, bc, parity);
     hipLaunchKernelGGL(k_batch_scatter, tg, blk, 0, s, tab, tile_sys, parity);
-    hipLaunchKernelGGL(k_batch_permute, tg, blk, 0, s, tab, tile_sys, parity);
-    hipLaunchKernelGGL(k_batch_commit, tg, blk, 0, s, tab, tile_sys, parity);
+    hipLaunchKernelGGL(k_batch_rank, tg, blk, 0, s, tab, tile_sys, parity);
     if (ev_sorted) (void)hipEventRecord(ev_sorted, s);
     if (bc.any_mat)
         hipLaunchKernelGGL(k_batch_nl_mtile, dim3((unsigned)ntiles * (kBlock / kTile)), dim3(kTile), 0, s, tab, tile_sys,
