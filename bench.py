@@ -54,9 +54,9 @@ ALG_BYTES = {"lj1m": 327.0, "kg2m": 213.0, "kg1k": 213.0, "sur1m": 819.0, "dpd1m
 STEP_KERNEL = {"lj1m": "k_step_fast (fused pair forces, velocity Verlet, reductions)",
                "kg2m": "k_step_fast_bonded (fused pair + bonded forces, velocity Verlet, reductions)",
                "kg1k": "k_step_fast_bonded (fused pair + bonded forces, velocity Verlet, reductions)",
-               "dpd1m": "k_step_gen (tabulated pair force, DPD pair thermostat, Lees-Edwards image and "
+               "dpd1m": "k_step_dpd (tabulated pair force, DPD pair thermostat, Lees-Edwards image and "
                         "crossing, velocity Verlet, reductions) with its velocity snapshot",
-               "adress1m": "k_step_gen (AdResS mix of LJ and a tabulated CG pair force, velocity Verlet, "
+               "adress1m": "k_step_adress (AdResS mix of LJ and a tabulated CG pair force, velocity Verlet, "
                            "reductions)"}
 # The surrogate's force stage is bound by vector ALU issue (counters: VALU
 # busy 95-100 % in the descriptor and pair-force kernels), so it is priced in

@@ -3,8 +3,9 @@
 // The handle plans the cell grid, carves the caller's workspace, keeps
 // host mirrors of the step counter and the position-buffer parity, and
 // enqueues every step as
-//     rebuild stage (8 kernels that return at once unless a particle moved
-//     more than skin/2) -> fused force+integrate kernel -> 1-block finalize
+//     rebuild stage (kernels that return at once unless a particle moved more
+//     than skin/2) -> fused force+integrate kernel, whose first block writes the
+//     previous step's record
 // on the caller's stream, optionally replayed from a hipGraph of two steps.
 #include <math.h>
 #include <stdio.h>
