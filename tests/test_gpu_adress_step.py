@@ -1,5 +1,4 @@
-"""The step kernel of an AdResS fluid of one particle type, in blocks of 64 and
-of 256 threads, at sizes that leave the last wavefront and the last batch of a
+"""The step kernel of an AdResS fluid of one particle type, at sizes that leave the last wavefront and the last batch of a
 row ragged, with a tabulated pair in place of the LJ one and with bonds, against
 the FP64 oracle: forces within 1e-5 per particle of the sum of the atomistic,
 coarse-grained and bonded force magnitudes, energies and the virial within 1e-5
@@ -66,3 +65,30 @@ def test_adress_step_kernel_forces(cells, drop, block, table, bonded):
     for k in ("e_pair", "e_bond"):
         assert abs(o[k] - oo[k]) <= TOL * abs(oo[k]), k
     assert abs(o["virial"] - oo["virial"]) <= TOL * oo["virial_abs"]
+
+
+def test_adress_forces_in_large_blocks_equal_the_generic_kernel():
+    """Above 65,536 particles (blocks of 256): forces of one particle type
+    against the same particles as two types of the same parameters, which take
+    the generic kernel.  The jittered lattice at density 0.8442 has 55
+    neighbours within 2.5 whose term magnitudes sum to under 4,000 (24 / r at
+    contact, 12 of them): forces agree within 1e-5 of that."""
+    pos, box = inputs.fcc_lattice(26, 0.8442, jitter=0.1, seed=14)
+    pos = np.ascontiguousarray(pos[:-3])
+    n = pos.shape[0]
+    assert n > 65536
+    zone = (0.5 * box[0], 0.15 * box[0], 0.2 * box[0])
+    r = np.linspace(0.0, 2.0, 500)
+    out = []
+    for ntypes in (1, 2):
+        rows = {(a, b): lj_pair(rc=2.5, caprad=0.85) for a in range(ntypes) for b in range(a, ntypes)}
+        types = None if ntypes == 1 else (np.arange(n) % 2).astype(np.int32)
+        s = System(pos, box, types=types, n_types=ntypes, pair=rows, masses=(1.0,) * ntypes, skin=0.3,
+                   table_points=512, adress=zone)
+        for a, b in rows:
+            s.set_cg_table(a, b, 7.5 * (1.0 - r / 2.0) ** 2, 7.5 * (1.0 - r / 2.0), 0.0, 2.0)
+        out.append(s.forces())
+        s.close()
+    print("max |dF| %.2e of max |F| %.1f" % (np.abs(out[0] - out[1]).max(), np.abs(out[1]).max()), flush=True)
+    assert np.abs(out[0] - out[1]).max() <= TOL * 4000.0
+    assert np.abs(out[1]).max() > 10.0

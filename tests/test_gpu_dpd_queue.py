@@ -1,8 +1,7 @@
 """The DPD step of one particle type collects the neighbours within reach in a
 queue of 32 per lane before it computes their forces: rows that fill it more
 than once, rows shorter than one batch of eight, a tabulated pair beside the
-thermostat, and bonds (some across the sheared boundary), in blocks of 64 and of
-256 threads.  One step from the same state and noise against the FP64 oracle's:
+thermostat, and bonds (some across the sheared boundary).  One step from the same state and noise against the FP64 oracle's:
 a force error dF_i moves x by dt^2/(2m) dF_i and the half-step velocity by
 dt/(2m) dF_i.  |dF_i| is at most 1e-5 times the sum of the force-term
 magnitudes, and, since these forces vanish at their cutoffs, for each neighbour
@@ -76,3 +75,36 @@ def test_dpd_step_against_oracle(rho, rc_d, rate, block, table, bonded):
     print("%d particles: |dx| / bound %.3f, |dv| / bound %.3f, max |Fd| %.2f" % (
         n, (dx / bx).max(), (dv / bv).max(), np.abs(Fd).max()), flush=True)
     assert np.all(dx <= bx) and np.all(dv <= bv)
+
+
+@pytest.mark.parametrize("rate", [0.0, 0.4])
+def test_dpd_step_in_large_blocks_equals_the_generic_step(rate):
+    """Above 65,536 particles (blocks of 256): one step of one particle type
+    against the same particles as two types of the same parameters, which take
+    the generic kernel.  About 13 terms of at most ~100 (sigma |theta| /
+    sqrt(dt)) each act on a particle: forces agree within 1e-5 of 30 x 100."""
+    n, dt = 70001, 0.01
+    L = (n / 3.0) ** (1.0 / 3.0)
+    box = np.array([L, L, L])
+    pos = inputs.random_positions(n, box, seed=42)
+    vel = inputs.maxwell_boltzmann(n, 1.0, seed=42)
+    vel[:, 0] += rate * (pos[:, 1] - 0.5 * L)
+    r = np.linspace(0.1, 1.0, 200)
+    u, f = 12.5 * (1.0 - r) ** 2, 25.0 * (1.0 - r)
+    out = []
+    for ntypes in (1, 2):
+        rows = {(a, b): lj_pair(eps=0.0, rc=1.0) for a in range(ntypes) for b in range(a, ntypes)}
+        types = None if ntypes == 1 else (np.arange(n) % 2).astype(np.int32)
+        s = System(pos, box, vel, types=types, n_types=ntypes, pair=rows, masses=(1.0,) * ntypes, skin=0.3, dt=dt,
+                   integrator="dpd", temperature=1.0, gamma=4.5, seed=9, dpd_rc=1.0, shear_rate=rate, table_points=256)
+        for a, b in rows:
+            s.set_pair_table(a, b, u, f, 0.1)
+        s.step(1)
+        out.append(s.get_state())
+        s.close()
+    dx = out[0]["pos"] - out[1]["pos"]
+    dx -= box * np.round(dx / box)
+    dF = TOL * 30 * 100.0
+    print("|dx| %.2e, |dv| %.2e" % (np.abs(dx).max(), np.abs(out[0]["vel"] - out[1]["vel"]).max()), flush=True)
+    assert np.abs(dx).max() <= dt * dt / 2 * dF and np.abs(out[0]["vel"] - out[1]["vel"]).max() <= dt / 2 * dF
+    assert np.abs(out[0]["vel"] - vel).max() > 0.1
