@@ -361,7 +361,7 @@ def single_record(name, a, w, s):
                    "integrator": w["integrator"],
                    "precision": "FP32 pair/bonded math, FP64 positions, velocities and reductions",
                    "parallelism": "single GPU", "cell_factor": plan["cell_factor"],
-                   "cells_per_side": plan["cells"][0], "list_build": plan["nl_build"],
+                   "cells_per_side": plan["cells"][0], "list_build": plan["list_build"],
                    "list_capacity": plan["nl_capacity"]},
         "timing": "value and ms_per_step: md_step replaying its two-step hipGraph (no events); roofline and "
                   "breakdown: a second pass of the same steps launched kernel by kernel with HIP events",

@@ -88,11 +88,13 @@ enum { MD_FP64 = 0, MD_FP32 = 1 };       /* md_config.force_precision */
 #define MD_CFG_NL_PER_PARTICLE 0x4 /* build the Verlet list one particle per lane */
 #define MD_CFG_NL_TILES 0x8        /* build it one wavefront per 64-particle tile (boxes of
                                       fewer than 2 cell_factor + 2 cells per side still build
-                                      per particle).  Default: planned by occupancy, tiles when
-                                      cells of side rc+skin hold >= 8 particles on average; the
-                                      build itself may take tiles for sparser systems and for
-                                      batch members.  Both builds give the same lists, entry
-                                      for entry, for equal cells */
+                                      per particle).  Default, with neither flag: one wavefront
+                                      per particle for unsheared systems of up to 20,000
+                                      particles, else tiles when cells of side rc+skin hold
+                                      >= 5 particles on average, else per particle; a batch
+                                      takes tiles for its members (md_plan_list_build says
+                                      which a configuration takes).  All builds give the same
+                                      lists for equal cells, entry for entry without shear */
 
 /* One type pair of the LennardJones / LennardJonesCapped potential
  * (section "Example usage"): u(r) = 4 eps [(sigma/r)^12 - (sigma/r)^6] - shift
@@ -212,14 +214,21 @@ md_status md_workspace_bytes(const md_config* cfg, size_t* bytes);
  * MD_CFG_NL_* flags.  Returns the same errors as md_workspace_bytes. */
 #define MD_NL_BUILD_PER_PARTICLE 0 /* one particle per lane */
 #define MD_NL_BUILD_TILES 1        /* one wavefront per 64-particle tile */
+#define MD_NL_BUILD_WAVE 2         /* one wavefront per particle (small systems) */
 typedef struct md_plan {
     int32_t cells[3];          /* cells per side */
     int32_t cell_factor;       /* 1 or 2: cells of side >= list_radius / cell_factor */
     int32_t nl_capacity;       /* list slots per particle */
-    int32_t nl_build;          /* MD_NL_BUILD_* */
+    int32_t nl_build;          /* MD_NL_BUILD_PER_PARTICLE or MD_NL_BUILD_TILES: the build of
+                                  systems too large for MD_NL_BUILD_WAVE; smaller ones
+                                  report what larger ones of their density take */
     double list_radius;        /* max(rc, list_cutoff) + skin */
 } md_plan;
 md_status md_plan_config(const md_config* cfg, md_plan* out);
+
+/* The list build that a handle of this configuration runs, *build one of
+ * MD_NL_BUILD_*.  Host arithmetic only; the errors of md_plan_config. */
+md_status md_plan_list_build(const md_config* cfg, int32_t* build);
 
 /* Create a simulation (storage.addParticles + decompose of the paper).
  *   pos, vel      device, FP64 [N][3], particle-id (tag) order; positions may

@@ -214,17 +214,12 @@ static md_status plan_geom(const md_config* c, Geom* g, std::string* why) {
     const double rv = fmax(fmax(rc_max_of(c), c->list_cutoff), c->integrator == MD_DPD ? c->dpd_rc : 0.0) + c->skin;
     g->rv2 = rv * rv;
     g->disp2 = (0.5 * c->skin) * (0.5 * c->skin);
-    // List build: dense systems (>= 8 particles expected in a cell of side
-    // rv) one wavefront per 64-particle tile, others one particle per lane,
-    // both on cells of side rv; half-cutoff sub-cells only when the box holds
-    // fewer than 3 cells of side rv per axis.  Measured on MI355X (2M-bead
-    // melt, 3 beads per cell): the per-particle build on cells of side rv
-    // beats half-cutoff sub-cells by 12% in whole-step throughput (fewer
-    // stencil rows, each a memory round trip) and the tile build, whose
-    // shared candidate stream is 2.4-7.7x longer than a lane's own.
+    // Cells of side rv; half-cutoff sub-cells only when the box holds fewer
+    // than 3 cells of side rv per axis.  Measured on MI355X (2M-bead melt, 3
+    // beads per cell): the per-particle build on cells of side rv beats
+    // half-cutoff sub-cells by 12% in whole-step throughput (fewer stencil
+    // rows, each a memory round trip).
     const double density = (double)c->n_particles / (c->box[0] * c->box[1] * c->box[2]);
-    const bool per_particle = (c->flags & MD_CFG_NL_PER_PARTICLE) != 0;
-    const bool dense = density * rv * rv * rv >= 8.0 && !per_particle;
     g->kc = c->cell_factor;
     if (g->kc == 0) {
         bool fit1 = true, fit2 = true;
@@ -273,13 +268,11 @@ static md_status plan_geom(const md_config* c, Geom* g, std::string* why) {
         if (cap > 4096) cap = 4096;
         g->cap = cap;
     }
-    g->nl_tile = (!per_particle && ((c->flags & MD_CFG_NL_TILES) || (dense && g->kc == 1))) ? 1 : 0;
     g->le = c->shear_rate != 0.0 ? 1 : 0;
     g->le_rate_Ly = c->shear_rate * c->box[1];
     g->le_dt = c->dt;
     g->skin = c->skin;
     g->table_points = c->table_points;
-    if (g->le) g->nl_tile = 0;   // the sheared stencil is built one particle per lane
     // Matrix-core build from 5 particles per cell of side rv on: it tests a
     // tile's whole row of candidates, the per-particle build only a lane's own
     // 27 cells.  Measured per build: 6.6 per cell (sheared DPD fluid, 1M) 217
@@ -287,7 +280,9 @@ static md_status plan_geom(const md_config* c, Geom* g, std::string* why) {
     // 2M) 472 against 396 us.  Its coordinates relative to a segment's centre
     // are minimum images only with 2 kc + 2 cells per side; smaller boxes build
     // one particle per lane.
-    g->nl_mat = (density * rv * rv * rv >= 5.0 || (c->flags & MD_CFG_NL_TILES)) && mat_build_fits(c, g) ? 1 : 0;
+    g->nl_dense = (density * rv * rv * rv >= 5.0 || (c->flags & MD_CFG_NL_TILES)) &&
+                  !(c->flags & MD_CFG_NL_PER_PARTICLE) ? 1 : 0;
+    g->nl_mat = g->nl_dense && mat_build_fits(c, g) ? 1 : 0;
     // One wavefront per particle for small systems, which leave the GPU idle
     // one particle per lane.  Measured per md_build_neighbors call (LJ, tiles
     // against this): 2,048 particles 116 / 34 us, 16,384 78 / 53, 33,333 75 /
@@ -808,8 +803,19 @@ md_status md_plan_config(const md_config* cfg, md_plan* out) {
     for (int d = 0; d < 3; ++d) out->cells[d] = g.nc[d];
     out->cell_factor = g.kc;
     out->nl_capacity = g.cap;
-    out->nl_build = g.nl_tile ? MD_NL_BUILD_TILES : MD_NL_BUILD_PER_PARTICLE;
+    const bool tiles = (g.nl_wave ? g.nl_dense : g.nl_mat) && (g.kc == 1 || (cfg->flags & MD_CFG_NL_TILES));
+    out->nl_build = tiles ? MD_NL_BUILD_TILES : MD_NL_BUILD_PER_PARTICLE;
     out->list_radius = sqrt(g.rv2);
+    return MD_OK;
+}
+
+md_status md_plan_list_build(const md_config* cfg, int32_t* build) {
+    if (!build) return fail(nullptr, MD_ERR_ARG, "build is NULL");
+    Geom g;
+    std::string why;
+    md_status st = plan_geom(cfg, &g, &why);
+    if (st != MD_OK) return fail(nullptr, st, why);
+    *build = list_build(g);
     return MD_OK;
 }
 

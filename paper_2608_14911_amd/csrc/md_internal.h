@@ -102,7 +102,7 @@ struct Geom {
     double qs[3];           // 2^32 / L
     float ql[3];            // L / 2^32
     float rv2lo, rv2hi;     // fixed-point list test band; FP64 test in between
-    int32_t nl_tile;        // the plan's list build (md_plan.nl_build)
+    int32_t nl_dense;       // dense enough for one wavefront per 64-particle tile
     int32_t nl_mat;         // the list is built on the matrix cores, one wavefront per
                             // 64-particle tile; 0: one particle per lane
     int32_t nl_wave;        // a small system's list: one wavefront per particle
@@ -117,6 +117,12 @@ struct Geom {
     double skin;
     int32_t table_points;   // row length of Bufs::tab
 };
+
+// The list build a handle runs: MD_NL_BUILD_*.
+inline int list_build(const Geom& g) {
+    if (g.nl_wave) return MD_NL_BUILD_WAVE;
+    return g.nl_mat ? MD_NL_BUILD_TILES : MD_NL_BUILD_PER_PARTICLE;
+}
 
 struct Bufs {
     DevCtl* ctl;

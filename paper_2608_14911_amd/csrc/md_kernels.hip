@@ -3200,12 +3200,13 @@ hipError_t launch_rebuild(const Geom& g, const Bufs& b, int parity, int bonded, 
     if (ev_sorted) (void)hipEventRecord(ev_sorted, s);
     const int64_t nt = (g.n + kTile - 1) / kTile;
     const dim3 tiles((unsigned)(nt < kNlGrid ? nt : kNlGrid));
-    if (g.nl_wave)
+    const int build = list_build(g);
+    if (build == MD_NL_BUILD_WAVE)
         hipLaunchKernelGGL(k_nl_wave, dim3((unsigned)((g.n + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0, s, g, b,
                            parity, bonded);
-    else if (g.nl_mat && g.le)
+    else if (build == MD_NL_BUILD_TILES && g.le)
         hipLaunchKernelGGL(k_nl_mtile<true>, tiles, dim3(kTile), 0, s, g, b, parity, bonded);
-    else if (g.nl_mat)
+    else if (build == MD_NL_BUILD_TILES)
         hipLaunchKernelGGL(k_nl_mtile<false>, tiles, dim3(kTile), 0, s, g, b, parity, bonded);
     else if (g.le)
         hipLaunchKernelGGL(k_nl_build_le, dim3(grid_for(g.n, 1 << 20)), dim3(kBlock), 0, s, g, b, parity, bonded);

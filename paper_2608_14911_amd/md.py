@@ -58,7 +58,8 @@ MD_SUR_BF16 = 1
 MD_PAIR_PLAIN = 0
 MD_PAIR_SURROGATE = 1
 
-EXPORTED = ["md_workspace_bytes", "md_plan_config", "md_init", "md_set_params", "md_build_neighbors", "md_forces",
+EXPORTED = ["md_workspace_bytes", "md_plan_config", "md_plan_list_build", "md_init", "md_set_params",
+            "md_build_neighbors", "md_forces",
             "md_step", "md_observables", "md_history", "md_get_state", "md_set_state",
             "md_get_neighbors", "md_status_check", "md_timing_enable", "md_timing_read",
             "md_destroy", "md_status_string", "md_last_error", "md_sur_set", "md_sur_get",
@@ -119,6 +120,8 @@ class md_plan(ctypes.Structure):
 
 MD_NL_BUILD_PER_PARTICLE = 0
 MD_NL_BUILD_TILES = 1
+MD_NL_BUILD_WAVE = 2
+NL_BUILD_NAMES = {MD_NL_BUILD_PER_PARTICLE: "per_particle", MD_NL_BUILD_TILES: "tiles", MD_NL_BUILD_WAVE: "wave"}
 
 
 class MDError(RuntimeError):
@@ -143,6 +146,7 @@ def lib():
     sig = {
         "md_workspace_bytes": [ctypes.POINTER(md_config), ctypes.POINTER(SZ)],
         "md_plan_config": [ctypes.POINTER(md_config), ctypes.POINTER(md_plan)],
+        "md_plan_list_build": [ctypes.POINTER(md_config), ctypes.POINTER(I32)],
         "md_init": [ctypes.POINTER(md_config), P, P, P, P, P, P, P, SZ, P, ctypes.POINTER(P)],
         "md_init_static": [ctypes.POINTER(md_config), P, P, P, P, P, P, P, ctypes.POINTER(P)],
         "md_set_params": [P, ctypes.POINTER(md_config)],
@@ -271,12 +275,16 @@ def md_workspace_bytes(cfg):
 
 
 def md_plan_config(cfg):
-    """Cell grid and list build the configuration resolves to (dict)."""
+    """Cell grid and list build the configuration resolves to (dict);
+    ``list_build`` is the build a handle runs ("wave", "tiles" or
+    "per_particle"), ``nl_build`` md_plan's name for its density."""
     p = md_plan()
+    build = ctypes.c_int32()
     _check(lib().md_plan_config(ctypes.byref(cfg), ctypes.byref(p)), "md_plan_config")
+    _check(lib().md_plan_list_build(ctypes.byref(cfg), ctypes.byref(build)), "md_plan_list_build")
     return {"cells": list(p.cells), "cell_factor": p.cell_factor, "nl_capacity": p.nl_capacity,
             "nl_build": "tiles" if p.nl_build == MD_NL_BUILD_TILES else "per_particle",
-            "list_radius": p.list_radius}
+            "list_radius": p.list_radius, "list_build": NL_BUILD_NAMES[build.value]}
 
 
 def md_init(cfg, pos, vel, type, mass_by_type, bonds, angles, workspace, ws_bytes, stream):
