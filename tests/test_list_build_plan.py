@@ -61,3 +61,11 @@ def test_arguments():
         md.md_plan_config(cfg)
     assert md.lib().md_plan_list_build(ctypes.byref(cfg), ctypes.byref(b)) == md.lib().md_plan_config(
         ctypes.byref(cfg), ctypes.byref(md.md_plan()))
+
+
+@pytest.mark.parametrize("n,rho,kw", [(1048576, 0.8442, LJ), (200000, 3.0, dict(LJ, pair={(0, 0): (1.0, 1.0, 1.0, 0.0, 0.0)})),
+                                      (200000, 3.0, dict(LJ, pair={(0, 0): (1.0, 1.0, 1.0, 0.0, 0.0)}, shear_rate=0.1))])
+def test_half_cells_are_built_per_particle_unless_tiles_are_asked_for(n, rho, kw):
+    assert plan(n, rho, cell_factor=2, **kw)["list_build"] == "per_particle"
+    assert plan(n, rho, cell_factor=2, flags=md.MD_CFG_NL_TILES, **kw)["list_build"] == "tiles"
+    assert plan(n, rho, **kw)["list_build"] == "tiles"
