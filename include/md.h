@@ -466,6 +466,10 @@ typedef struct md_batch_s* md_batch;
 
 /* Workspace bytes for the batch cfgs[0..nsys-1] (host arithmetic only). */
 md_status md_batch_workspace_bytes(const md_config* cfgs, int32_t nsys, size_t* bytes);
+/* The list build of each member, build[nsys] of MD_NL_BUILD_PER_PARTICLE and
+ * MD_NL_BUILD_TILES.  Host arithmetic only; the errors of
+ * md_batch_workspace_bytes. */
+md_status md_batch_plan_list_build(const md_config* cfgs, int32_t nsys, int32_t* build);
 /* Create the batch.  pos[s], vel[s]: device FP64 [n_s][3]; mass_by_type[s]:
  * host FP64 [1]; bonds[s] / angles[s]: host int32 topology as for md_init, or
  * bonds / angles NULL for none; workspace: device, >= md_batch_workspace_bytes(),

@@ -1538,6 +1538,17 @@ md_status plan_batch(const md_config* cfgs, int32_t nsys, BatchPlan* p, std::str
     return MD_OK;
 }
 
+// Whether a batch member's list is built on the matrix cores: wherever that
+// fits, but for small sparse members, whose few candidates one lane has
+// tested before a wavefront is through a tile's shared rows.  Melts alone, 8 or
+// 48 members, 40 steps, tiles against per particle: 500 beads 3,509 / 2,957 and
+// 4,890 / 3,692 us, 1,500 2,915 / 2,762 and 4,240 / 4,069, 4,000 2,904 / 2,989
+// and 4,640 / 4,771, 30,000 3,391 / 3,575 and 10,496 / 11,486, 250,000 (8)
+// 12,527 / 13,476.
+bool batch_mat(const md_config* c, const Geom& g) {
+    return mat_build_fits(c, &g) && (g.nl_dense || g.n > 2048);
+}
+
 md_status bfail(md_batch b, md_status st, const std::string& msg) {
     if (b) b->err = msg;
     g_last_error = msg;
@@ -1595,6 +1606,17 @@ md_status md_batch_workspace_bytes(const md_config* cfgs, int32_t nsys, size_t* 
     md_status st = plan_batch(cfgs, nsys, &p, &why);
     if (st != MD_OK) return fail(nullptr, st, why);
     *bytes = p.total;
+    return MD_OK;
+}
+
+md_status md_batch_plan_list_build(const md_config* cfgs, int32_t nsys, int32_t* build) {
+    if (!build) return fail(nullptr, MD_ERR_ARG, "build is NULL");
+    BatchPlan p;
+    std::string why;
+    md_status st = plan_batch(cfgs, nsys, &p, &why);
+    if (st != MD_OK) return fail(nullptr, st, why);
+    for (int s = 0; s < nsys; ++s)
+        build[s] = batch_mat(&cfgs[s], p.g[s]) ? MD_NL_BUILD_TILES : MD_NL_BUILD_PER_PARTICLE;
     return MD_OK;
 }
 
@@ -1665,11 +1687,7 @@ md_status md_batch_init(const md_config* cfgs, int32_t nsys, const double* const
             md_batch_destroy(b);
             return fail(nullptr, r, m);
         }
-        // one build kernel for all members wherever it fits: sparse members
-        // alone would build faster per particle, but a second launch's tail
-        // costs more (48 uneven replicas: 93 us per step in one kernel, 69 + 68
-        // us in two)
-        h->g.nl_mat = mat_build_fits(&cfgs[s], &h->g) ? 1 : 0;
+        h->g.nl_mat = batch_mat(&cfgs[s], h->g) ? 1 : 0;
         b->sys.push_back(h);
     }
     std::vector<SysEntry> tab((size_t)4 * nsys);
@@ -1690,8 +1708,6 @@ md_status md_batch_init(const md_config* cfgs, int32_t nsys, const double* const
                 e.c_off = p.c_off[s];
             }
         for (int64_t t = 0; t < p.ntiles[s]; ++t) tiles[p.tile0[s] + t] = s;
-        if (h->g.nl_mat) b->bc.any_mat = 1;
-        else b->bc.any_one = 1;
     }
     if (hipMemcpyAsync(b->tabs[0][0], tab.data(), sizeof(SysEntry) * tab.size(), hipMemcpyHostToDevice,
                        b->stream) != hipSuccess ||

@@ -332,7 +332,6 @@ struct BatchCells {
     int64_t* c_off;         // [nsys + 1] first cell per system
     int32_t* base;          // [nsys] scan prefix at each system's first cell
     int32_t nsys;
-    int32_t any_mat, any_one;   // some member's list is built on the matrix cores / per particle
 };
 
 // ev_sorted (or null) is recorded between the cell sort and the list build

@@ -681,8 +681,9 @@ __device__ __forceinline__ void nl_store4(int32_t (*buf)[64], int ln, int32_t* _
         }
     }
 }
+// nlbuf: kNlLds + 1 rows of the wavefront's LDS.
 __device__ __forceinline__ void nl_one(const Geom& g, const Bufs& b, int64_t i, int parity, int bonded,
-                                       int& local_max, bool& overflow) {
+                                       int32_t (*nlbuf)[64], int& local_max, bool& overflow) {
     const int64_t n = g.n;
     const double4* __restrict__ x = b.x[parity];
     const int4* __restrict__ xq = b.xq[parity];
@@ -703,10 +704,9 @@ __device__ __forceinline__ void nl_one(const Geom& g, const Bufs& b, int64_t i, 
         // hits of the lanes fall in different iterations, so direct stores
         // would cost one partly masked store instruction per hit event.
         // Row kNlLds is a spare that takes the stores of candidates that miss.
-        __shared__ int32_t nlbuf[kBlock / 64][kNlLds + 1][64];
-        const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+        const int ln = threadIdx.x & 63;
         auto put = [&](int k, int j) {
-            if (k < kNlLds) nlbuf[wv][k][ln] = j;
+            if (k < kNlLds) nlbuf[k][ln] = j;
             else nlrow[nl_off(k)] = j;
         };
         // Cells cx-kc .. cx+kc of one (y, z) row are consecutive in the cell
@@ -740,7 +740,7 @@ __device__ __forceinline__ void nl_one(const Geom& g, const Bufs& b, int64_t i, 
                     for (int u = 0; u < 4; ++u)
                         if (band[u]) in[u] = exact_r2(g, xi, x[j + u]) < g.rv2;
                 }
-                nl_store4<true>(nlbuf[wv], ln, nlrow, g.cap, in, j, cnt);
+                nl_store4<true>(nlbuf, ln, nlrow, g.cap, in, j, cnt);
             }
         };
         const int xlo = cx - kc, xhi = cx + kc;   // inclusive cell range along x
@@ -791,7 +791,7 @@ __device__ __forceinline__ void nl_one(const Geom& g, const Bufs& b, int64_t i, 
         for (int k = cnt; k < nslot; ++k) put(k, (int)i);
 #pragma unroll
         for (int k = 0; k < kNlLds; ++k)
-            if (k < nslot) nlrow[nl_off(k)] = nlbuf[wv][k][ln];
+            if (k < nslot) nlrow[nl_off(k)] = nlbuf[k][ln];
         if (bonded) remap_bonded(b, n, i);
     }
 }
@@ -813,10 +813,12 @@ __device__ __forceinline__ void nl_epilogue(const Bufs& b, int local_max, bool o
 }
 
 __global__ void __launch_bounds__(kBlock) k_nl_build(Geom g, Bufs b, int parity, int bonded) {
+    __shared__ int32_t nlbuf[kBlock / 64][kNlLds + 1][64];
     if (!rebuild_requested(b, parity)) return;
     int local_max = 0;
     bool overflow = false;
-    for (int64_t i = gtid_xcd(); i < g.n; i += gstride()) nl_one(g, b, i, parity, bonded, local_max, overflow);
+    for (int64_t i = gtid_xcd(); i < g.n; i += gstride())
+        nl_one(g, b, i, parity, bonded, nlbuf[threadIdx.x >> 6], local_max, overflow);
     nl_epilogue(b, local_max, overflow);
 }
 
@@ -3048,33 +3050,33 @@ __global__ void __launch_bounds__(kBlock) k_batch_rank(const SysEntry* __restric
     if (r.i < r.e->a.g.n) rank_one(r.e->a.g, b, r.i, parity, r.e->bonded);
 }
 
-// Members whose list is built one particle per lane.
-__global__ void __launch_bounds__(kBlock) k_batch_nl(const SysEntry* __restrict__ tab,
-                                                     const int32_t* __restrict__ tile_sys, int parity) {
-    const TileRef r = tile_ref_spread(tab, tile_sys);
-    const Bufs& b = r.e->a.b;
-    const Geom& g = r.e->a.g;
-    if (g.nl_mat || !rebuild_requested(b, parity)) return;
-    int local_max = 0;
-    bool overflow = false;
-    if (r.i < g.n) nl_one(g, b, r.i, parity, r.e->bonded, local_max, overflow);
-    nl_epilogue(b, local_max, overflow);
-}
-
-// Members whose list is built on the matrix cores: one wavefront per
-// 64-particle tile, four to a tile of the batch.
-__global__ void __launch_bounds__(kTile) k_batch_nl_mtile(const SysEntry* __restrict__ tab,
-                                                          const int32_t* __restrict__ tile_sys, int parity) {
-    __shared__ NlWave sh;
+// The members' lists, one wavefront per 64 particles (four to a tile of the
+// batch): on the matrix cores or one particle per lane, by member.  Both in
+// one launch: a batch's build lasts as long as its slowest wavefront, in two
+// launches as long as the sum of theirs (48 LJ members of 600 to 1,540
+// particles, some too small for the matrix cores, 40 steps: 15.5 ms in two
+// launches, 12.0 in one).
+union NlBatch {
+    NlWave mat;
+    int32_t rows[kNlLds + 1][64];
+};
+__global__ void __launch_bounds__(kTile) k_batch_nl(const SysEntry* __restrict__ tab,
+                                                    const int32_t* __restrict__ tile_sys, int parity) {
+    __shared__ NlBatch sh;
     const SysEntry* e = tab + tile_sys[blockIdx.x / (kBlock / kTile)];
     const Bufs& b = e->a.b;
     const Geom& g = e->a.g;
-    if (!g.nl_mat || !rebuild_requested(b, parity)) return;
+    if (!rebuild_requested(b, parity)) return;
     const int64_t t = (int64_t)blockIdx.x - e->tile0 * (kBlock / kTile);
     if (t * kTile >= g.n) return;
     int local_max = 0;
     bool overflow = false;
-    nl_mtile<false>(g, b, t, parity, e->bonded, sh, LeNl{0.0, 0.0, 0u}, local_max, overflow);
+    if (g.nl_mat) {
+        nl_mtile<false>(g, b, t, parity, e->bonded, sh.mat, LeNl{0.0, 0.0, 0u}, local_max, overflow);
+    } else {
+        const int64_t i = t * kTile + threadIdx.x;
+        if (i < g.n) nl_one(g, b, i, parity, e->bonded, sh.rows, local_max, overflow);
+    }
     nl_epilogue(b, local_max, overflow);
 }
 
@@ -3373,10 +3375,7 @@ hipError_t launch_batch_rebuild(const BatchCells& bc, const SysEntry* tab, const
     hipLaunchKernelGGL(k_batch_scatter, tg, blk, 0, s, tab, tile_sys, parity);
     hipLaunchKernelGGL(k_batch_rank, tg, blk, 0, s, tab, tile_sys, parity);
     if (ev_sorted) (void)hipEventRecord(ev_sorted, s);
-    if (bc.any_mat)
-        hipLaunchKernelGGL(k_batch_nl_mtile, dim3((unsigned)ntiles * (kBlock / kTile)), dim3(kTile), 0, s, tab, tile_sys,
-                           parity);
-    if (bc.any_one) hipLaunchKernelGGL(k_batch_nl, tg, blk, 0, s, tab, tile_sys, parity);
+    hipLaunchKernelGGL(k_batch_nl, dim3((unsigned)ntiles * (kBlock / kTile)), dim3(kTile), 0, s, tab, tile_sys, parity);
     return hipGetLastError();
 }
 

@@ -64,7 +64,7 @@ EXPORTED = ["md_workspace_bytes", "md_plan_config", "md_plan_list_build", "md_in
             "md_get_neighbors", "md_status_check", "md_timing_enable", "md_timing_read",
             "md_destroy", "md_status_string", "md_last_error", "md_sur_set", "md_sur_get",
             "md_set_pair_mode", "md_sur_descriptors", "md_sur_desc_stats", "md_sur_mlp_eval", "md_sur_pair_forces", "md_sur_loss_grad",
-            "md_sur_adam", "md_batch_workspace_bytes", "md_batch_init", "md_batch_step",
+            "md_sur_adam", "md_batch_workspace_bytes", "md_batch_plan_list_build", "md_batch_init", "md_batch_step",
             "md_batch_observables", "md_batch_get_state", "md_batch_destroy", "md_batch_last_error",
             "md_batch_timing_enable", "md_batch_timing_read", "md_init_static", "md_set_pair_table",
             "md_set_angle_table", "md_set_angle_subens", "md_set_cg_table"]
@@ -182,6 +182,7 @@ def lib():
         f.restype = ctypes.c_int32
     for name, args in {
         "md_batch_workspace_bytes": [P, I32, ctypes.POINTER(SZ)],
+        "md_batch_plan_list_build": [P, I32, P],
         "md_batch_init": [P, I32, P, P, P, P, P, P, SZ, P, ctypes.POINTER(P)],
         "md_batch_step": [P, I64],
         "md_batch_observables": [P, P],
@@ -463,6 +464,15 @@ def md_batch_workspace_bytes(cfgs):
     _bcheck(lib().md_batch_workspace_bytes(ctypes.cast(arr, ctypes.c_void_p), len(cfgs), ctypes.byref(n)),
             "md_batch_workspace_bytes")
     return n.value
+
+
+def md_batch_plan_list_build(cfgs):
+    """The list build of each member ("tiles" or "per_particle")."""
+    arr = (md_config * len(cfgs))(*cfgs)
+    out = (ctypes.c_int32 * len(cfgs))()
+    _bcheck(lib().md_batch_plan_list_build(ctypes.cast(arr, ctypes.c_void_p), len(cfgs),
+                                           ctypes.cast(out, ctypes.c_void_p)), "md_batch_plan_list_build")
+    return [NL_BUILD_NAMES[k] for k in out]
 
 
 def md_batch_init(cfgs, pos_ptrs, vel_ptrs, masses, bonds, angles, workspace, ws_bytes, stream):

@@ -69,3 +69,20 @@ def test_half_cells_are_built_per_particle_unless_tiles_are_asked_for(n, rho, kw
     assert plan(n, rho, cell_factor=2, **kw)["list_build"] == "per_particle"
     assert plan(n, rho, cell_factor=2, flags=md.MD_CFG_NL_TILES, **kw)["list_build"] == "tiles"
     assert plan(n, rho, **kw)["list_build"] == "tiles"
+
+
+def test_batch_members_take_tiles_but_for_small_sparse_ones():
+    cfg = lambda n, rho, **kw: md.make_config(n, [(n / rho) ** (1 / 3)] * 3, **kw)
+    skin5 = dict(WCA, skin=0.5)
+    cases = [(cfg(500, 0.85, **skin5), "per_particle"), (cfg(2048, 0.85, **skin5), "per_particle"),
+             (cfg(2049, 0.85, **skin5), "tiles"), (cfg(250000, 0.85, **skin5), "tiles"),
+             (cfg(500, 0.85, flags=md.MD_CFG_NL_TILES, **skin5), "tiles"),
+             (cfg(30000, 0.85, flags=md.MD_CFG_NL_PER_PARTICLE, **skin5), "per_particle"),
+             (cfg(1000, 0.8, **LJ), "per_particle"),     # 3 cells per side
+             (cfg(1500, 0.8, **LJ), "tiles"), (cfg(30000, 0.8, **LJ), "tiles"),
+             (cfg(30000, 0.8, cell_factor=2, **LJ), "per_particle")]
+    assert md.md_batch_plan_list_build([c for c, _ in cases]) == [b for _, b in cases]
+    for c, b in cases:      # a member's build does not depend on the others
+        assert md.md_batch_plan_list_build([c]) == [b]
+    with pytest.raises(md.MDError):
+        md.md_batch_plan_list_build([])
