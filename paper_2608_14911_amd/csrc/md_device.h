@@ -36,6 +36,16 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// LDS written by some lanes of a wavefront is read by others of it next (or
+// the other way round).  The wavefront runs in lockstep and its LDS accesses
+// complete in order, so this emits nothing; it keeps the compiler from moving
+// LDS accesses across.
+__device__ __forceinline__ void wave_exchange() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 __device__ __forceinline__ int64_t gtid() { return (int64_t)blockIdx.x * blockDim.x + threadIdx.x; }
 
 // Workgroups are handed to the 8 XCDs round-robin (block b -> XCD b % 8),

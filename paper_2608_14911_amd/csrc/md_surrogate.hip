@@ -503,7 +503,7 @@ __global__ void __launch_bounds__(kMlpBlock) k_sur_mlp(SurBufs s, const float* _
 #pragma unroll
             for (int e = 0; e < 4; ++e) sB[p * S64 + c + e] = Act<BF16>::put(valid ? xv[e] : 0.f);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
         float z[16], s1[16];
         tile_gemm<64, 32, S64, BF16 ? kSW1 : kPF1>(sB, wi.W1(), z, p, hq);
 #pragma unroll
@@ -514,7 +514,7 @@ __global__ void __launch_bounds__(kMlpBlock) k_sur_mlp(SurBufs s, const float* _
             s1[v] = sg * (1.f + zz * (1.f - sg));
             sA[p * S64 + h] = Act<BF16>::put(zz * sg);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
         tile_gemm<64, 64, S64, BF16 ? kSW64 : kPF64>(sA, wi.W2(), z, p, hq);
         float e = 0.f;
 #pragma unroll
@@ -531,14 +531,14 @@ __global__ void __launch_bounds__(kMlpBlock) k_sur_mlp(SurBufs s, const float* _
             if (eout) eout[base + p] = e + b3;
             esum += (double)(e + b3);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
         tile_gemm<64, 64, S64, BF16 ? kSW64 : kPF64>(sB, wi.W2T(), z, p, hq);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int h = 16 * (v >> 2) + 4 * hq + (v & 3);
             sA[p * S64 + h] = Act<BF16>::put(z[v] * s1[v]);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
         float gx[8];
         tile_gemm<32, 64, S64, BF16 ? kSW64 : kPF64>(sA, wi.W1T(), gx, p, hq);
         if (valid) {
@@ -550,7 +550,7 @@ __global__ void __launch_bounds__(kMlpBlock) k_sur_mlp(SurBufs s, const float* _
                     make_float4(gx[4 * cb] * is.x, gx[4 * cb + 1] * is.y, gx[4 * cb + 2] * is.z, gx[4 * cb + 3] * is.w);
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
     }
     if (epart) {
         // one column per block; the grid's columns past it hold nothing
