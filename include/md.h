@@ -129,10 +129,12 @@ typedef struct md_config {
     int32_t nl_capacity;       /* neighbours per particle, rounded up to a multiple
                                   of 8 (rows are streamed in batches of 8 slots);
                                   0 = from density */
-    int32_t block_size;        /* particles (threads) per block of the FP32 fast force
-                                  kernels: 64, 128, 256 or 512; 0 = 64 up to 65,536
-                                  particles, else 256.  The other force kernels take the
-                                  latter, batches 256.  Changes cost only: every
+    int32_t block_size;        /* particles (threads) per block of the force kernels:
+                                  64, 128, 256 or 512; 0 = 64 up to 65,536 particles, else
+                                  256.  128 and 512 are for the FP32 fast kernels (one
+                                  type, cubic box, no capping, tables, DPD, shear or
+                                  AdResS); the others take them as 0.  The surrogate's
+                                  and batches' kernels keep 256.  Changes cost only: every
                                   particle's force is computed alone, and only the order
                                   of the FP64 energy/virial block sums follows it */
     int32_t flags;             /* MD_CFG_* */

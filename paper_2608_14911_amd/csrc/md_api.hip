@@ -564,9 +564,11 @@ static void fill_sur_const(SurConst* c) {
 // wavefront per block, so that all CUs share the gathers: measured per step,
 // 256 against 64 threads: 33,333 LJ particles 18.3 / 17.2 us, 10,000 capped
 // ones 15.8 / 14.8; at 131,000 (FP64) the two are equal.
+// The FP32 fast kernels take every size asked for, the others 64 and 256.
 static int block_of(md_handle h) {
-    const int automatic = h->g.n <= kSmallBlocks ? 64 : kBlock;
-    return h->use_fast && !h->fp64 && h->cfg.block_size ? h->cfg.block_size : automatic;
+    const int ask = h->cfg.block_size;
+    const bool takes = (h->use_fast && !h->fp64) ? ask != 0 : (ask == 64 || ask == kBlock);
+    return takes ? ask : h->g.n <= kSmallBlocks ? 64 : kBlock;
 }
 
 // Force stage: the plain fused kernel, or the surrogate's network stage
