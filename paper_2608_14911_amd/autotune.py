@@ -31,7 +31,10 @@ import time
 ARCH = "gfx950"
 CACHE_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "data", "autotune_cache.json")
 SKINS = (0.3, 0.4, 0.5)
-# (cell factor, list build)
+# (cell factor, list build).  A caller may add (0, "auto"), the library's own
+# choice: unsheared systems of up to 20,000 particles then build one wavefront
+# per particle, which no entry here names (2,048 LJ particles, per build: tiles
+# 116 us, automatic 34).
 BUILDS = ((1, "tiles"), (1, "per_particle"), (2, "per_particle"))
 BLOCKS = (64, 128, 256, 512)
 
@@ -155,7 +158,7 @@ def tune(members, steps=40, skins=SKINS, builds=BUILDS, log=None, path=CACHE_PAT
     cache."""
     keys = sorted({member_key(m) for m in members})
     choice = {k: (next(m["skin"] for m in members if member_key(m) == k), 0, "auto") for k in keys}
-    table = []
+    table, measured = [], set()
     for k in keys:
         best = None
         for skin in skins:
@@ -175,10 +178,11 @@ def tune(members, steps=40, skins=SKINS, builds=BUILDS, log=None, path=CACHE_PAT
                     best = (ms, skin, cf, build)
         if best is not None:
             choice[k] = best[1:]
+            measured.add(k)
     if write:
         cache = load_cache(path)
         for k, (skin, cf, build) in choice.items():
-            if build != "auto":
+            if k in measured:
                 cache[k] = {"skin": skin, "cell_factor": cf, "nl_build": build, "source": "batch"}
         save_cache(cache, path)
     return choice, table
@@ -200,8 +204,8 @@ def tune_system(make, n, rho, rc, kind, steps=40, builds=BUILDS, blocks=BLOCKS, 
     choice, such as the surrogate's descriptor list).  ``make(cell_factor,
     flags)`` -- or ``make(cell_factor, flags, skin)`` with ``skins`` --
     returns a fresh System.  Skins, cells and builds are tried first at 256
-    particles per block, then the block sizes on the winner (switched in
-    place with md_set_params, which changes cost only).  Returns
+    particles per block, then the block sizes on the winner (both set with
+    md_set_params, which changes cost only).  Returns
     ((cell_factor, nl_build, block_size, skin), table)."""
     from .system import nl_build_flags
     table, best = [], None
@@ -213,6 +217,7 @@ def tune_system(make, n, rho, rc, kind, steps=40, builds=BUILDS, blocks=BLOCKS, 
                 if log:
                     log("autotune %s cf %d %s: skipped (%s)" % (kind, cf, build, e))
                 continue
+            s.set_params(block_size=256)    # 0 would run another size than the table says
             ms = _time_system(s, steps)
             skin = s.cfg.skin
             s.close()
