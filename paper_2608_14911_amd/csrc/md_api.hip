@@ -11,6 +11,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <string>
@@ -379,7 +380,7 @@ static size_t carve(const md_config* c, const Geom& g, int step_grid, uint8_t* b
         u.u = (float*)take(sizeof(float) * kSurNB * n);
         u.f = (float4*)take(sizeof(float4) * n);
         u.delta = (float4*)take(sizeof(float4) * n);
-        u.part = (double*)take(sizeof(double) * kSurPart * (size_t)step_grid);
+        u.part = (double*)take(sizeof(double) * (size_t)std::max(2 * step_grid, sur_loss_parts(n)));
         u.loss = (double*)take(sizeof(double) * 4);
         u.w = (float*)take(sizeof(float) * kSurNPpad);
         u.wp = (float*)take(sizeof(float) * kPrepF);
@@ -612,7 +613,7 @@ static hipError_t launch_stage_finalize(md_handle h, int parity, int mode, const
         block = block_of(h);
         nb = step_launch_grid(h->g.n, block);
     }
-    return launch_finalize(h->b, parity, nb, block, mode, spart, tensor, h->stream, 1);
+    return launch_finalize(h->b, parity, nb, block, mode, spart, tensor, h->stream);
 }
 
 // A step's record is left to the next step's kernel, and to finish_steps at the

@@ -244,7 +244,6 @@ constexpr int kQW1 = 0, kQW1T = 64 * kSW1, kQW2 = kQW1T + 32 * kSW64, kQW2T = kQ
 constexpr int kMS1 = 40, kMS64 = 72;
 constexpr int kM1 = 0, kM2 = 64 * kMS1, kM2T = kM2 + 64 * kMS64, kM1T = kM2T + 64 * kMS64,
               kPrepM = kM1T + 32 * kMS64;
-constexpr int kSurPart = 9;                 // E, W, tensor[6], loss
 constexpr int kSurGradBlocks = 256;         // blocks of the double-backward kernel
 constexpr int kSurMomBlocks = 256;          // blocks of the descriptor-moment kernel (partials in gpart)
 static_assert(kSurMomBlocks * 2 * kSurNB * 2 <= kSurGradBlocks * kSurNPpad, "moment partials fit in gpart");
@@ -256,7 +255,7 @@ struct SurBufs {
     float* u;           // [N][32] training: dL/da_i
     float4* f;          // [N] surrogate pair force
     float4* delta;      // [N] training: dL/dF_i
-    double* part;       // [kSurPart][step grid] block partials
+    double* part;       // [2][step grid] energy partials by parity, or the sur_loss_parts(n) of a loss
     double* loss;       // [1] loss accumulated over the frames of a call
     float* w;           // [kSurNPpad] master weights
     float* wp;          // [kPrepF] prepared FP32 weights
@@ -360,11 +359,10 @@ int step_grid(int64_t n);
 // per block (the FP32 fast kernels take 64, 128, 256 or 512, the others 64 or 256)
 int step_launch_grid(int64_t n, int block);
 constexpr int64_t kSmallBlocks = 65536;     // systems up to this take 64-thread blocks by default
-// spart: surrogate partials (row 0 energy; with spart_rows 8 also virial and
-// tensor rows), or nullptr
+// spart: the step's surrogate energy partials, or nullptr
 // block: threads of the step kernel's blocks; parity: of the step finalized
 hipError_t launch_finalize(const Bufs& b, int parity, int nblocks, int block, int mode, const double* spart,
-                           int tensor, hipStream_t s, int spart_rows = 8);
+                           int tensor, hipStream_t s);
 hipError_t launch_overwrite_state(const Geom& g, const Bufs& b, int parity, const double* pos,
                                   const double* vel, const int32_t* image, hipStream_t s);
 hipError_t launch_get_state(const Geom& g, const Bufs& b, int parity, double* pos, double* vel,

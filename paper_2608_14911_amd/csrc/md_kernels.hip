@@ -1803,8 +1803,7 @@ __device__ __forceinline__ void block_epilogue(const StepArgs& a, const double* 
 constexpr int kFinal = 1024;
 constexpr int kNaccStep = A_VIR + 1;
 template <int BS, int NACC>
-__device__ __forceinline__ void finalize_body(const Bufs& b, int parity, int nblocks, int mode, const double* spart,
-                                              int spart_rows) {
+__device__ __forceinline__ void finalize_body(const Bufs& b, int parity, int nblocks, int mode, const double* spart) {
     __shared__ double red[BS / 64][NACC];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const double* __restrict__ part = b.partials + (int64_t)partial_row(NACC, parity) * nblocks;
@@ -1823,19 +1822,11 @@ __device__ __forceinline__ void finalize_body(const Bufs& b, int parity, int nbl
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int k = 0; k < NACC; ++k) s[k] += v[r][k];
-        if (spart) {
-            // surrogate pair energy (row 0), virial (row 1) and tensor (rows 2..7)
+        if (spart)
             for (int r = 0; r < 4; ++r) {
                 const int blk = blk0 + r * BS + threadIdx.x;
-                if (blk >= nblocks) continue;
-                s[A_EPAIR] += spart[blk];
-                if (spart_rows > 1) {
-                    s[A_VIR] += spart[(int64_t)nblocks + blk];
-                    if (NACC == kNacc)
-                        for (int k = 0; k < 6; ++k) s[(A_TXX + k) % NACC] += spart[(int64_t)(2 + k) * nblocks + blk];
-                }
+                if (blk < nblocks) s[A_EPAIR] += spart[blk];
             }
-        }
     }
 #pragma unroll
     for (int k = 0; k < NACC; ++k) {
@@ -1883,9 +1874,8 @@ __device__ __forceinline__ void finalize_body(const Bufs& b, int parity, int nbl
 }
 
 template <int BS, int NACC>
-__global__ void __launch_bounds__(BS) k_finalize(Bufs b, int parity, int nblocks, int mode, const double* spart,
-                                                 int spart_rows) {
-    finalize_body<BS, NACC>(b, parity, nblocks, mode, spart, spart_rows);
+__global__ void __launch_bounds__(BS) k_finalize(Bufs b, int parity, int nblocks, int mode, const double* spart) {
+    finalize_body<BS, NACC>(b, parity, nblocks, mode, spart);
 }
 
 // Block index and grid of a step kernel without the block that writes the
@@ -1896,7 +1886,7 @@ __device__ __forceinline__ bool finalize_block(const StepArgs& a, int& blk, int&
     blk = (int)blockIdx.x - a.fin;
     grid = (int)gridDim.x - a.fin;
     if (blk >= 0) return false;
-    if (a.b.ctl->fin_prev) finalize_body<BS, kNaccStep>(a.b, a.parity ^ 1, grid, MODE_PREV, a.fin_spart, 1);
+    if (a.b.ctl->fin_prev) finalize_body<BS, kNaccStep>(a.b, a.parity ^ 1, grid, MODE_PREV, a.fin_spart);
     return true;
 }
 
@@ -3092,7 +3082,7 @@ k_batch_step(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_
     if ((int)blockIdx.x < nfin) {   // a member's previous step's record
         const SysEntry& e = tab[blockIdx.x];
         if (e.a.b.ctl->fin_prev)
-            finalize_body<kBlock, kNaccStep>(e.a.b, e.a.parity ^ 1, e.ntiles, MODE_PREV, nullptr, 1);
+            finalize_body<kBlock, kNaccStep>(e.a.b, e.a.parity ^ 1, e.ntiles, MODE_PREV, nullptr);
         return;
     }
     const TileRef r = tile_ref(tab, tile_sys, (int)blockIdx.x - nfin, (int)gridDim.x - nfin);
@@ -3111,7 +3101,7 @@ k_batch_step(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_
 template <int BS, int NACC>
 __global__ void __launch_bounds__(BS) k_batch_finalize(const SysEntry* __restrict__ tab, int mode) {
     const SysEntry& e = tab[blockIdx.x];
-    finalize_body<BS, NACC>(e.a.b, e.a.parity, e.ntiles, mode, nullptr, 1);
+    finalize_body<BS, NACC>(e.a.b, e.a.parity, e.ntiles, mode, nullptr);
 }
 
 __global__ void k_batch_gather_obs(const SysEntry* __restrict__ tab, int nsys, double* out) {
@@ -3330,9 +3320,9 @@ hipError_t launch_step(const StepArgs& a, int fp64, int single_type, int bonded,
 }
 
 hipError_t launch_finalize(const Bufs& b, int parity, int nblocks, int block, int mode, const double* spart,
-                           int tensor, hipStream_t s, int spart_rows) {
+                           int tensor, hipStream_t s) {
 #define MD_FIN(BS, NA) \
-    hipLaunchKernelGGL((k_finalize<BS, NA>), dim3(1), dim3(BS), 0, s, b, parity, nblocks, mode, spart, spart_rows)
+    hipLaunchKernelGGL((k_finalize<BS, NA>), dim3(1), dim3(BS), 0, s, b, parity, nblocks, mode, spart)
     if (tensor) MD_FIN(kFinal, kNacc);
     else if (block == 64) MD_FIN(64, kNaccStep);
     else if (block == 128) MD_FIN(128, kNaccStep);
