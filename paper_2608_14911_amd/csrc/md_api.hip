@@ -1567,16 +1567,15 @@ md_status bfail(md_batch b, md_status st, const std::string& msg) {
 
 hipError_t batch_enqueue_step(md_batch b, const EvQuad* q = nullptr) {
     if (q) (void)hipEventRecord(q->e[0], b->stream);
-    const int defer = b->timing ? 0 : 1;
     SysEntry* const tab = b->tabs[0][b->parity];
     hipError_t e = launch_batch_rebuild(b->bc, tab, b->tile_sys, b->ntiles, b->parity, 1, b->stream,
                                         q ? q->e[4] : nullptr);
     if (e != hipSuccess) return e;
     if (q) (void)hipEventRecord(q->e[1], b->stream);
-    e = launch_batch_step(tab, b->tile_sys, b->ntiles, b->nsys, defer, 0, b->stream);
+    e = launch_batch_step(tab, b->tile_sys, b->ntiles, 0, b->stream);
     if (e != hipSuccess) return e;
     if (q) (void)hipEventRecord(q->e[2], b->stream);
-    if (!defer && (e = launch_batch_finalize(tab, b->nsys, MODE_STEP, b->stream)) != hipSuccess) return e;
+    if (b->timing && (e = launch_batch_end(b->bc, b->stream)) != hipSuccess) return e;
     if (q) (void)hipEventRecord(q->e[3], b->stream);
     b->parity ^= 1;
     b->host_step += 1;
@@ -1774,9 +1773,8 @@ md_status md_batch_step(md_batch b, int64_t nsteps) {
         BHIP_TRY(b, batch_enqueue_step(b));
         --left;
     }
-    // the last step's records (the others were written by the steps after them)
-    if (nsteps > 0 && !b->timing)
-        BHIP_TRY(b, launch_batch_finalize(b->tabs[0][b->parity ^ 1], b->nsys, MODE_STEP, b->stream));
+    // the last step ends here (the others ended with the steps after them)
+    if (nsteps > 0 && !b->timing) BHIP_TRY(b, launch_batch_end(b->bc, b->stream));
     batch_sync_members(b);
     return MD_OK;
 }
@@ -1785,8 +1783,8 @@ md_status md_batch_observables(md_batch b, md_obs* out) {
     if (!b || !out) return fail(nullptr, MD_ERR_ARG, "NULL argument");
     SysEntry* to = b->tabs[1][b->parity];
     BHIP_TRY(b, launch_batch_rebuild(b->bc, to, b->tile_sys, b->ntiles, b->parity, 0, b->stream));
-    BHIP_TRY(b, launch_batch_step(to, b->tile_sys, b->ntiles, b->nsys, 0, 1, b->stream));
-    BHIP_TRY(b, launch_batch_finalize(to, b->nsys, MODE_OBSERVE, b->stream));
+    BHIP_TRY(b, launch_batch_step(to, b->tile_sys, b->ntiles, 1, b->stream));
+    BHIP_TRY(b, launch_batch_observe(to, b->nsys, b->stream));
     BHIP_TRY(b, launch_batch_gather_obs(to, b->nsys, b->obs, b->stream));
     std::vector<double> rec((size_t)kHistRec * b->nsys);
     BHIP_TRY(b, hipMemcpyAsync(rec.data(), b->obs, sizeof(double) * rec.size(), hipMemcpyDeviceToHost, b->stream));

@@ -336,10 +336,10 @@ struct BatchCells {
 // ev_sorted (or null) is recorded between the cell sort and the list build
 hipError_t launch_batch_rebuild(const BatchCells& bc, const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles,
                                 int parity, int advance, hipStream_t s, hipEvent_t ev_sorted = nullptr);
-// fin: the launch also writes every member's previous step's record
-hipError_t launch_batch_step(const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles, int nsys, int fin,
-                             int tensor, hipStream_t s);
-hipError_t launch_batch_finalize(const SysEntry* tab, int nsys, int mode, hipStream_t s);
+hipError_t launch_batch_step(const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles, int tensor, hipStream_t s);
+hipError_t launch_batch_observe(const SysEntry* tab, int nsys, hipStream_t s);
+// ends the last of the steps launched so far
+hipError_t launch_batch_end(const BatchCells& bc, hipStream_t s);
 hipError_t launch_batch_gather_obs(const SysEntry* tab, int nsys, double* out, hipStream_t s);
 
 // launchers (md_kernels.hip)

@@ -2961,9 +2961,8 @@ struct TileRef {
     int64_t i;      // particle inside the system
 };
 
-__device__ __forceinline__ TileRef tile_ref(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_sys,
-                                            int blk, int grid) {
-    const int64_t t = xcd_block(blk, grid);
+__device__ __forceinline__ TileRef tile_ref(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_sys) {
+    const int64_t t = xcd_block(blockIdx.x, gridDim.x);
     const SysEntry* e = tab + tile_sys[t];
     const int64_t lt = t - e->tile0;
     return TileRef{e, lt, lt * kBlock + threadIdx.x};
@@ -3078,14 +3077,8 @@ __global__ void __launch_bounds__(kTile) k_batch_nl(const SysEntry* __restrict__
 // melts): 637 -> 615 us per step for the 256-replica batch.
 template <bool TENSOR>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
-k_batch_step(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_sys, int nfin) {
-    if ((int)blockIdx.x < nfin) {   // a member's previous step's record
-        const SysEntry& e = tab[blockIdx.x];
-        if (e.a.b.ctl->fin_prev)
-            finalize_body<kBlock, kNaccStep>(e.a.b, e.a.parity ^ 1, e.ntiles, MODE_PREV, nullptr);
-        return;
-    }
-    const TileRef r = tile_ref(tab, tile_sys, (int)blockIdx.x - nfin, (int)gridDim.x - nfin);
+k_batch_step(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_sys) {
+    const TileRef r = tile_ref(tab, tile_sys);
     const StepArgs& a = r.e->a;
     double acc[kNacc];
 #pragma unroll
@@ -3098,10 +3091,20 @@ k_batch_step(const SysEntry* __restrict__ tab, const int32_t* __restrict__ tile_
     block_epilogue(a, acc, flag_reb, flag_bond, flag_nf, TENSOR ? kNacc : kNaccStep, r.lt, r.e->ntiles);
 }
 
-template <int BS, int NACC>
-__global__ void __launch_bounds__(BS) k_batch_finalize(const SysEntry* __restrict__ tab, int mode) {
+__global__ void __launch_bounds__(kFinal) k_batch_observe(const SysEntry* __restrict__ tab) {
     const SysEntry& e = tab[blockIdx.x];
-    finalize_body<BS, NACC>(e.a.b, e.a.parity, e.ntiles, mode, nullptr);
+    finalize_body<kFinal, kNacc>(e.a.b, e.a.parity, e.ntiles, MODE_OBSERVE, nullptr);
+}
+
+// The end of a call's last step.  Members keep no per-step records (a batch has
+// no history call), so only the counters move.
+__global__ void k_batch_end(BatchCells bc) {
+    for (int s = threadIdx.x; s < bc.nsys; s += blockDim.x) {
+        DevCtl* c = bc.tab[s].a.b.ctl;
+        c->step += 1;
+        c->vel_half = 1;
+        c->ran = 0;
+    }
 }
 
 __global__ void k_batch_gather_obs(const SysEntry* __restrict__ tab, int nsys, double* out) {
@@ -3369,20 +3372,20 @@ hipError_t launch_batch_rebuild(const BatchCells& bc, const SysEntry* tab, const
     return hipGetLastError();
 }
 
-hipError_t launch_batch_step(const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles, int nsys, int fin,
-                             int tensor, hipStream_t s) {
-    const int nfin = fin ? nsys : 0;
-    const dim3 grid((unsigned)(ntiles + nfin));
-    if (tensor) hipLaunchKernelGGL(k_batch_step<true>, grid, dim3(kBlock), 0, s, tab, tile_sys, nfin);
-    else hipLaunchKernelGGL(k_batch_step<false>, grid, dim3(kBlock), 0, s, tab, tile_sys, nfin);
+hipError_t launch_batch_step(const SysEntry* tab, const int32_t* tile_sys, int64_t ntiles, int tensor, hipStream_t s) {
+    const dim3 grid((unsigned)ntiles);
+    if (tensor) hipLaunchKernelGGL(k_batch_step<true>, grid, dim3(kBlock), 0, s, tab, tile_sys);
+    else hipLaunchKernelGGL(k_batch_step<false>, grid, dim3(kBlock), 0, s, tab, tile_sys);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_finalize(const SysEntry* tab, int nsys, int mode, hipStream_t s) {
-    if (mode == MODE_STEP)
-        hipLaunchKernelGGL((k_batch_finalize<kBlock, kNaccStep>), dim3(nsys), dim3(kBlock), 0, s, tab, mode);
-    else
-        hipLaunchKernelGGL((k_batch_finalize<kFinal, kNacc>), dim3(nsys), dim3(kFinal), 0, s, tab, mode);
+hipError_t launch_batch_observe(const SysEntry* tab, int nsys, hipStream_t s) {
+    hipLaunchKernelGGL(k_batch_observe, dim3(nsys), dim3(kFinal), 0, s, tab);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_end(const BatchCells& bc, hipStream_t s) {
+    hipLaunchKernelGGL(k_batch_end, dim3(1), dim3(256), 0, s, bc);
     return hipGetLastError();
 }
 
