@@ -650,9 +650,9 @@ constexpr int kNlLds = 24;  // row slots staged in LDS by the per-particle build
 // no branch; past them (LIST_PATH) one masked store per hit; otherwise, and
 // for the group that crosses from LDS to the list, the general path.  Hits
 // beyond the capacity are counted, not stored.  The list-only path pays where
-// rows run well past the LDS slots (the dense fluids of a batch); where rows
-// end near them (the sheared DPD fluid, ~28 slots) the lanes split over three
-// paths and it cost 11 % of the build, so that build leaves it out.
+// rows run well past the LDS slots (dense fluids on half cells or by flag);
+// where rows end near them (the sheared DPD fluid, ~28 slots) the lanes split
+// over three paths and it cost 11 % of the build, so that build leaves it out.
 template <bool LIST_PATH>
 __device__ __forceinline__ void nl_store4(int32_t (*buf)[64], int ln, int32_t* __restrict__ nlrow, int cap,
                                           const bool (&in)[4], int j0, int& cnt) {
@@ -1095,9 +1095,10 @@ __global__ void __launch_bounds__(kBlock) k_nl_build_le(Geom g, Bufs b, int pari
 
 // ------------------------------------------------------------------ list build on the matrix cores
 //
-// The lists of nl_one (and nl_one_le) built one wavefront per 64-particle tile
-// of the sorted order (the tile of the list layout), entry for entry.  The
-// tile's particles lie in a few consecutive cells; lanes of one (y, z) cell row
+// The lists of nl_one, entry for entry, and the sets of nl_one_le (under shear
+// a segment's range may cover a whole row where a lane's own does not, and the
+// row then starts elsewhere), built one wavefront per 64-particle tile of the
+// sorted order (the tile of the list layout).  The tile's particles lie in a few consecutive cells; lanes of one (y, z) cell row
 // form a segment whose x-cells span [x0, x1].  The segment's candidates are
 // the particles of cells [x0 - kc, x1 + kc] in each of the (2kc+1)^2
 // neighbouring rows, in nl_one's order (rows z-major, a wrapped x-range high
@@ -2464,8 +2465,8 @@ __global__ void __launch_bounds__(BS) k_step_gen(const StepArgs a) {
     block_epilogue<BS>(a, acc, flag_reb, flag_bond, flag_nf, tensor ? kNacc : kNaccStep, blk, grid);
 }
 
-// The DPD step of one particle type (k_step_gen's arithmetic, MODE_STEP, without
-// AdResS), sheared (LE) or not.  Drawing theta_ij costs ten rounds of quarter-
+// The DPD step of one particle type (k_step_gen's terms in its order, some
+// contracted otherwise; MODE_STEP, without AdResS), sheared (LE) or not.  Drawing theta_ij costs ten rounds of quarter-
 // rate multiplies, and the lanes of a wavefront draw together: walking the list
 // with the draw inside spends it on nearly every slot, though less than half
 // of a lane's slots are within the cutoffs ((1 / 1.3)^3 at skin 0.3).  So each
@@ -2657,13 +2658,17 @@ __global__ void __launch_bounds__(BS) k_step_dpd(const StepArgs a) {
 }
 
 // The AdResS step of one particle type without shear or DPD (k_step_gen's
-// arithmetic), the pair and coarse-grained tables in LDS.  Bound by VALU issue
+// terms in its order; the mix is contracted otherwise, so forces differ in
+// rounding, about 1e-6 of the largest), the pair and coarse-grained tables in
+// LDS.  Bound by VALU issue
 // and the texture-data path together.  Records are gathered four at a time and
 // the registers held to five wavefronts per SIMD: 299,997 particles are 4,688
 // wavefronts, which four per SIMD (4,096 on the card) run in two rounds.  Step
 // kernel at that size, density 0.8442: k_step_gen 125 us; here 104 us with four
 // per SIMD and eight records, 101 with five and eight, 89-92 with five and
-// four.  Leaving out the force of weight 0 in wavefronts that need one force
+// four.  20 steps with their list builds, this tree against the generic kernel
+// and the builds before it: 1.74x at 4,000 particles, 1.40x at 60,000, 1.31x at
+// 150,000, 1.28x at 500,000, 1.38x at 1,000,000.  Leaving out the force of weight 0 in wavefronts that need one force
 // only gained 2 us and was not worth three copies of the loop.
 template <bool BONDED, int BS>
 __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(5))) k_step_adress(const StepArgs a) {
